@@ -1,0 +1,86 @@
+"""Kernels at the edges of their tiles: line counts around a workgroup's lines,
+tables around a chunk of terms, mixtures around a stage of members, and the
+state exchange's truncation, against a library FFT, the oracle's mixture and
+the array that was set."""
+import math
+
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+HK = dict(qr_bins=64, q_lo=-30.0, q_hi=30.0, r_lo=-60.0, r_hi=60.0, log_bins=128, log10_lo=-8.0, log10_hi=5.0,
+          a_bins=256, a_lo=-60.0, a_hi=60.0, eps_ref=0.1, nu_ref=0.02)
+
+
+@pytest.mark.parametrize("n", [16, 256, 512, 1024])
+@pytest.mark.parametrize("prec", ["fp64", "fp32"])
+def test_pencils_around_a_workgroups_lines(n, prec):
+    import torch
+    import paper_2506_23712_amd as ens
+    T = max(256 // (n // 16), 16 if prec == "fp32" else 8)      # lines of a workgroup
+    dt = torch.complex64 if prec == "fp32" else torch.complex128
+    for lines in (T - 1, T, T + 1, 8 * T + 3):
+        rng = np.random.default_rng(n + lines)
+        x = torch.from_numpy(rng.standard_normal((n, lines)) + 1j * rng.standard_normal((n, lines))).to(dt)
+        ref = np.fft.fft(x.numpy().astype(np.complex128), axis=0)
+        got = ens.fft_pencils(x.cuda(), -1).cpu().numpy()
+        # one rounding per butterfly level, of values up to the largest output
+        tol = (6e-8 if prec == "fp32" else 1.2e-16) * 4 * math.log2(n)
+        assert np.max(np.abs(got - ref)) <= tol * np.max(np.abs(ref)), lines
+
+
+@pytest.mark.parametrize("M", [2, 16, 254, 256, 258, 1022, 1024, 1026, 65536])
+def test_lambda_density_transform_around_a_chunk_of_terms(M):
+    """The transform alone (a table that starts at lambda = 0, so that no phase
+    omega lam0 is rounded): each of the M terms is a product of three factors of
+    a rounding or two each, so the sum is within 8 eps of the sum of moduli."""
+    import torch
+    import paper_2506_23712_amd as ens
+    rng = np.random.default_rng(M)
+    phi = rng.standard_normal(M) + 1j * rng.standard_normal(M)
+    h = 6.0 / M
+    got = ens.lambda_pdf_from_cf(torch.from_numpy(phi).cuda(), 0.0, h).cpu().numpy()
+    ref = np.fft.fft(phi).real / (M * h)
+    assert np.max(np.abs(got - ref)) <= 8 * 1.2e-16 * np.abs(phi).sum() / (M * h)
+
+
+@pytest.mark.parametrize("count", [1, 127, 128, 129, 260])
+def test_mixture_around_a_stage_of_members(count):
+    import torch
+    import paper_2506_23712_amd as ens
+    from oracle import mixture as mx
+    rng = np.random.default_rng(count)
+    lams = list(rng.permutation(np.linspace(-2.0, 2.0, count)) if count > 1 else np.array([0.1]))
+    E = ens.Ensemble(hist=ens.HistSpec(**HK))
+    ms = [E.add_member(ens.MemberSpec(n=16, nu=0.02, eps_ref=0.1, lam=float(l), kf_hi=2.0, dt=0.01, seed=i))
+          for i, l in enumerate(lams)]
+    E.accumulate_stats()
+    got = [m.stats() for m in ms]
+    pdfs = [g[0].numpy()[:64 * 64] / (16 ** 3 * (60 / 64) * (120 / 64)) for g in got]
+    pdf = torch.linspace(0.1, 1.0, 900, dtype=torch.float64, device="cuda")
+    for res, w in ((E.mix(0.023, 1.0, mode=1 if count > 1 else 0), mx.weights(lams, 0.023, 1.0, mode=1 if count > 1 else 0)),
+                   (E.mix_table(pdf, -2.5, 0.005), mx.weights_from_table(lams, pdf.cpu().tolist(), -2.5, 0.005))):
+        assert np.allclose(res["weights"].numpy(), w, rtol=1e-12, atol=1e-16)
+        assert np.allclose(res["qr"].numpy().ravel(), np.array(mx.mix(w, pdfs)), rtol=1e-12, atol=1e-300)
+        m2 = sum(wi * g[1][1].item() / (3 * 16 ** 3) for wi, g in zip(w, got))
+        assert math.isclose(res["moments"][1].item(), m2, rel_tol=1e-12)
+    E.close()
+
+
+@pytest.mark.parametrize("n", [16, 32, 64, 128])
+@pytest.mark.parametrize("prec", ["fp64", "fp32"])
+def test_state_exchange_keeps_the_retained_modes_and_zeroes_the_rest(n, prec):
+    import torch
+    import paper_2506_23712_amd as ens
+    E = ens.Ensemble()
+    m = E.add_member(ens.MemberSpec(n=n, nu=0.02, precision=prec))
+    g = torch.Generator().manual_seed(n)
+    u = torch.randn((3, n, n, n // 2 + 1), generator=g, dtype=torch.complex128)
+    m.set_state(u)
+    got = m.state().cpu()
+    E.close()
+    f = torch.fft.fftfreq(n, 1.0 / n).abs() <= n // 3
+    keep = f.view(1, n, 1, 1) & f.view(1, 1, n, 1) & (torch.arange(n // 2 + 1) <= n // 3)
+    ref = torch.where(keep, u, torch.zeros_like(u))
+    assert torch.equal(got, ref if prec == "fp64" else ref.to(torch.complex64).to(torch.complex128))
