@@ -637,14 +637,21 @@ struct MixTable {
     double lam0, h;
 };
 
-__global__ void __launch_bounds__(256) k_mix_prep(MixIn *mi, long long nqr) {
-    __shared__ unsigned long long red[256];
-    unsigned long long s = 0;
+// Samples of a member: the sum of its QR counters (bins and specials), whole
+// numbers, so the order does not matter.  One workgroup per member; each of the
+// 1024 threads has four loads in flight (one load at a time by 256 threads took
+// 64 us for 48 members of 256 x 256 bins, this 11 us).
+__global__ void __launch_bounds__(1024) k_mix_prep(MixIn *mi, long long nqr) {
+    __shared__ unsigned long long red[1024];
     const unsigned long long *c = mi[blockIdx.x].counts;
-    for (long long i = threadIdx.x; i < nqr; i += 256) s += c[i];
-    red[threadIdx.x] = s;
+    unsigned long long s[4] = {0, 0, 0, 0};
+    for (long long i = threadIdx.x; i < nqr; i += 4096) {
+#pragma unroll
+        for (int u = 0; u < 4; u++) s[u] += i + 1024 * u < nqr ? c[i + 1024 * u] : 0ull;
+    }
+    red[threadIdx.x] = (s[0] + s[1]) + (s[2] + s[3]);
     __syncthreads();
-    for (int k = 128; k > 0; k >>= 1) {
+    for (int k = 512; k > 0; k >>= 1) {
         if ((int)threadIdx.x < k) red[threadIdx.x] += red[threadIdx.x + k];
         __syncthreads();
     }
@@ -686,8 +693,10 @@ static double truncated_mean(double c, double Z) {
 
 // Integral over [a, b) of a tabulated lambda density: samples p_j at
 // lam0 + j h (negative samples read as zero), linear in between, zero outside.
-// Segments are visited in increasing order.
+// The lanes of a wave take the segments in turn, and the lane sums are added in
+// a fixed butterfly; every lane returns the integral.
 __device__ double table_mass(const MixTable &t, double a, double b) {
+    const int lane = threadIdx.x & 63;
     const double x_end = t.lam0 + (t.M - 1) * t.h;
     const double lo = a > t.lam0 ? a : t.lam0, hi = b < x_end ? b : x_end;
     if (!(hi > lo)) return 0.0;
@@ -695,7 +704,7 @@ __device__ double table_mass(const MixTable &t, double a, double b) {
     if (s0 < 0) s0 = 0;
     if (s1 > t.M - 2) s1 = t.M - 2;
     double acc = 0.0;
-    for (int s = s0; s <= s1; s++) {
+    for (int s = s0 + lane; s <= s1; s += 64) {
         const double x0 = t.lam0 + s * t.h, x1 = x0 + t.h;
         const double u = lo > x0 ? lo : x0, v = hi < x1 ? hi : x1;
         if (!(v > u)) continue;
@@ -703,25 +712,36 @@ __device__ double table_mass(const MixTable &t, double a, double b) {
         const double fu = p0 + (p1 - p0) * (u - x0) / t.h, fv = p0 + (p1 - p0) * (v - x0) / t.h;
         acc += (v - u) * 0.5 * (fu + fv);
     }
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) acc += __shfl_xor(acc, off, 64);
     return acc;
 }
 
+// One workgroup.  Everything it looks at more than once (the lambdas, the
+// sorted order, the bin edges and the raw weights) is in LDS: read from memory,
+// the rank loop and the serial sum of the weights were chains of loads (225 us
+// for 48 members, now 18 us).  The masses under a tabulated density (mode 4)
+// are taken by one wave per member.
 __global__ void __launch_bounds__(1024) k_mix_weights(MixIn *mi, int count, double c, double Z, int mode, double qs,
                                                       double mu3, MixTable tab, double *out) {
-    __shared__ double raw[kMaxMix + 1];
+    __shared__ double raw[kMaxMix + 1], lam[kMaxMix + 1], ea[kMaxMix + 1], eb[kMaxMix + 1];
+    __shared__ int ord[kMaxMix + 1];
     const int i = threadIdx.x;
+    if (i < count) lam[i] = mi[i].lambda;
+    __syncthreads();
     double w = 0.0;
     if (i < count) {
-        const double li = mi[i].lambda;
+        const double li = lam[i];
         int rank = 0;
         double prev = -INFINITY, next = INFINITY;
         bool has_prev = false, has_next = false;
         for (int j = 0; j < count; j++) {
-            const double lj = mi[j].lambda;
+            const double lj = lam[j];
             const bool before = lj < li || (lj == li && j < i);
             if (before) { rank++; if (!has_prev || lj >= prev) { prev = lj; has_prev = true; } }
             else if (j != i) { if (!has_next || lj < next) { next = lj; has_next = true; } }
         }
+        ord[rank] = i;
         mi[rank].order = i;
         double a = has_prev ? 0.5 * (prev + li) : -INFINITY;
         double b = has_next ? 0.5 * (li + next) : INFINITY;
@@ -729,8 +749,10 @@ __global__ void __launch_bounds__(1024) k_mix_weights(MixIn *mi, int count, doub
             if (!has_prev) a = li - (b - li);
             if (!has_next) b = li + (li - a);
         }
+        ea[i] = a;
+        eb[i] = b;
         if (mode == 4) {
-            w = table_mass(tab, a, b);
+            // below, by whole waves
         } else if (mode == 2) {
             const double mu = -4.5 * c * Z, sig = sqrt(9.0 * c * Z);
             const double p = exp(-(li - mu) * (li - mu) / (2.0 * sig * sig)) / sig;
@@ -745,11 +767,19 @@ __global__ void __launch_bounds__(1024) k_mix_weights(MixIn *mi, int count, doub
             w = nmass(a, b, -4.5 * c * Z, sqrt(9.0 * c * Z));
         }
     }
-    raw[i] = w;
+    if (mode != 4) raw[i] = w;
     __syncthreads();
+    if (mode == 4) {
+        for (int k = i >> 6; k < count; k += 16) {
+            const double m = table_mass(tab, ea[k], eb[k]);
+            if ((i & 63) == 0) raw[k] = m;
+        }
+        __syncthreads();
+        if (i < count) w = raw[i];
+    }
     if (i == 0 && (mode == 1 || mode == 2 || mode == 4)) {
         double s = 0.0;
-        for (int r = 0; r < count; r++) s += raw[mi[r].order];
+        for (int r = 0; r < count; r++) s += raw[ord[r]];
         raw[kMaxMix] = s;    // count <= kMaxMix keeps this slot free
     }
     __syncthreads();
@@ -767,39 +797,42 @@ struct MixGeom {
     long long o_qr, o_le, o_lw, o_al, o_at, o_mom, o_der;
 };
 
-__global__ void __launch_bounds__(256) k_mix_pdf(const MixIn *__restrict__ mi, MixGeom g, double *out) {
-    const long long nqr = (long long)g.qb * g.qb;
-    const long long total = nqr + 2LL * g.lb + 2LL * g.ab;
-    const long long b = (long long)blockIdx.x * 256 + threadIdx.x;
-    if (b >= total) return;
-    long long src, dst;
-    double width, mult;
-    if (b < nqr) { src = b; dst = g.o_qr + b; width = g.area_qr; mult = 1.0; }
-    else if (b < nqr + g.lb) { src = g.off_le + (b - nqr); dst = g.o_le + (b - nqr); width = g.w_l; mult = 1.0; }
-    else if (b < nqr + 2 * g.lb) { const long long k = b - nqr - g.lb; src = g.off_lw + k; dst = g.o_lw + k; width = g.w_l; mult = 1.0; }
-    else if (b < nqr + 2 * g.lb + g.ab) { const long long k = b - nqr - 2 * g.lb; src = g.off_al + k; dst = g.o_al + k; width = g.w_a; mult = 3.0; }
-    else { const long long k = b - nqr - 2 * g.lb - g.ab; src = g.off_at + k; dst = g.o_at + k; width = g.w_a; mult = 6.0; }
-    double acc = 0.0;
-    for (int r = 0; r < g.count; r++) {
-        const MixIn &m = mi[mi[r].order];
-        const double n = m.ntot * mult;
-        if (n > 0.0) acc += m.w * ((double)m.counts[src] / (n * width));
+// The members of a mixture in sorted-lambda order, staged in LDS kMixStage at a
+// time: a member's counters (or moments), its weight and its sample count.
+// Read from the table in the loop, the pointer, weight and count of every
+// member were a chain of loads in front of each counter's load.
+constexpr int kMixStage = 128;
+struct MixRow {
+    const void *p;
+    double w, n;
+};
+__device__ __forceinline__ int stage_rows(MixRow *rows, const MixIn *mi, int r0, int count, bool moments) {
+    const int n = count - r0 < kMixStage ? count - r0 : kMixStage;
+    __syncthreads();                                           // the previous rows are read
+    for (int r = (int)threadIdx.x; r < n; r += (int)blockDim.x) {
+        const MixIn &m = mi[mi[r0 + r].order];
+        rows[r] = MixRow{moments ? (const void *)m.moments : (const void *)m.counts, m.w, m.ntot};
     }
-    out[dst] = acc;
+    __syncthreads();
+    return n;
 }
 
-__global__ void __launch_bounds__(64) k_mix_moments(const MixIn *__restrict__ mi, MixGeom g, double *out) {
-    __shared__ double mm[32];
+// Mixed mean moments and the ratios formed from them, by one workgroup.
+__device__ __forceinline__ void mix_moments(MixRow *rows, double *mm, const MixIn *mi, const MixGeom &g, double *out) {
     const int k = threadIdx.x;
-    if (k < 32) {
-        const double mult = k < 6 ? 3.0 : (k < 12 ? 6.0 : 1.0);
-        double acc = 0.0;
+    const double mult = k < 6 ? 3.0 : (k < 12 ? 6.0 : 1.0);
+    double acc = 0.0;
+    for (int r0 = 0; r0 < g.count; r0 += kMixStage) {
+        const int nr = stage_rows(rows, mi, r0, g.count, true);
         if (k < 26) {
-            for (int r = 0; r < g.count; r++) {
-                const MixIn &m = mi[mi[r].order];
-                if (m.ntot > 0.0) acc += m.w * (m.moments[k] / (m.ntot * mult));
+#pragma unroll 4
+            for (int r = 0; r < nr; r++) {
+                const double x = ((const double *)rows[r].p)[k];
+                if (rows[r].n > 0.0) acc += rows[r].w * (x / (rows[r].n * mult));
             }
         }
+    }
+    if (k < 32) {
         mm[k] = acc;
         out[g.o_mom + k] = acc;
     }
@@ -815,6 +848,40 @@ __global__ void __launch_bounds__(64) k_mix_moments(const MixIn *__restrict__ mi
         d[6] = mm[16];
         d[7] = 0.0;
     }
+}
+
+// One thread per bin; a member's counters are read whole lines at a time by
+// neighbouring bins, four members' loads in flight.  The last workgroup forms
+// the moments beside the bins (a launch of its own added its 20 us of chained
+// divisions to every mixture).
+__global__ void __launch_bounds__(256) k_mix_pdf(const MixIn *__restrict__ mi, MixGeom g, double *out) {
+    __shared__ MixRow rows[kMixStage];
+    __shared__ double mm[32];
+    if (blockIdx.x == gridDim.x - 1) {
+        mix_moments(rows, mm, mi, g, out);
+        return;
+    }
+    const long long nqr = (long long)g.qb * g.qb;
+    const long long total = nqr + 2LL * g.lb + 2LL * g.ab;
+    const long long b = (long long)blockIdx.x * 256 + threadIdx.x;
+    long long src = 0, dst = 0;
+    double width = 1.0, mult = 1.0;
+    if (b < nqr) { src = b; dst = g.o_qr + b; width = g.area_qr; mult = 1.0; }
+    else if (b < nqr + g.lb) { src = g.off_le + (b - nqr); dst = g.o_le + (b - nqr); width = g.w_l; mult = 1.0; }
+    else if (b < nqr + 2 * g.lb) { const long long k = b - nqr - g.lb; src = g.off_lw + k; dst = g.o_lw + k; width = g.w_l; mult = 1.0; }
+    else if (b < nqr + 2 * g.lb + g.ab) { const long long k = b - nqr - 2 * g.lb; src = g.off_al + k; dst = g.o_al + k; width = g.w_a; mult = 3.0; }
+    else if (b < total) { const long long k = b - nqr - 2 * g.lb - g.ab; src = g.off_at + k; dst = g.o_at + k; width = g.w_a; mult = 6.0; }
+    double acc = 0.0;
+    for (int r0 = 0; r0 < g.count; r0 += kMixStage) {
+        const int nr = stage_rows(rows, mi, r0, g.count, false);
+#pragma unroll 4
+        for (int r = 0; r < nr; r++) {
+            const double n = rows[r].n * mult;
+            const double x = (double)((const unsigned long long *)rows[r].p)[src];
+            if (n > 0.0) acc += rows[r].w * (x / (n * width));
+        }
+    }
+    if (b < total) out[dst] = acc;
 }
 
 size_t mix_scratch_bytes(int count) { return sizeof(MixIn) * (size_t)(count > 0 ? count : 1); }
@@ -900,7 +967,7 @@ static hipError_t run_mix(const MixIn *tbl, MixIn *mi, int count, const ens_hist
     if (e != hipSuccess) return e;
     e = hipStreamSynchronize(s);       // the host table may be reused on return
     if (e != hipSuccess) return e;
-    k_mix_prep<<<count, 256, 0, s>>>(mi, hg.off_le);
+    k_mix_prep<<<count, 1024, 0, s>>>(mi, hg.off_le);
     const double mu3 = (mode == 3 && Z > 0.0) ? truncated_mean(c, Z) : 0.0;
     MixTable tab;
     tab.p = table; tab.M = table_len; tab.lam0 = lam0; tab.h = dlam;
@@ -919,8 +986,7 @@ static hipError_t run_mix(const MixIn *tbl, MixIn *mi, int count, const ens_hist
     g.o_mom = g.o_at + hg.ab;
     g.o_der = g.o_mom + ENS_NMOM;
     const long long total = (long long)hg.qb * hg.qb + 2LL * hg.lb + 2LL * hg.ab;
-    k_mix_pdf<<<(unsigned)((total + 255) / 256), 256, 0, s>>>(mi, g, out);
-    k_mix_moments<<<1, 64, 0, s>>>(mi, g, out);
+    k_mix_pdf<<<(unsigned)((total + 255) / 256) + 1, 256, 0, s>>>(mi, g, out);
     return hipGetLastError();
 }
 
