@@ -183,7 +183,8 @@ ens_status ens_step(ens_ctx *ctx, const int32_t *members, int32_t count, int32_t
  * 2 y inverse, 3 x fused (c2r, u x omega, r2c), 4 y forward,
  * 5 z forward + projection + forcing + update, 6 end-of-step reduction.
  * With the fused z forward (pass 5 variant 1) the z inverse of stages 2 and
- * 3 runs inside pass 5 and is counted there. */
+ * 3 runs inside pass 5 and is counted there; with the plane pass (pass 3
+ * variant 5, n <= 64) passes 0, 2 and 4 run inside pass 3. */
 #define ENS_NPASS 7
 ens_status ens_profile_step(ens_ctx *ctx, const int32_t *members, int32_t count, void *stream,
                             double *ms_out);
@@ -203,12 +204,15 @@ ens_status ens_get_diag(ens_ctx *ctx, int32_t m, ens_diag *out);
  * variant 3 = the same with 16 values per thread for FP32 and 128 <= n <= 512,
  * else variant 2; variants 4 and 5 = the streamed pass with one wave per
  * workgroup and every transform exchange inside the wave, 16 or 8 (FP32) /
- * 8 or 4 (FP64) values per thread, n >= 64, else variant 2; variant 6 =
- * variant 4 with its inputs staged pairwise through two buffers, less LDS
- * per wave)
+ * 8 or 4 (FP64) values per thread, n >= 64, else variant 2 - but for n <= 64
+ * variant 5 is the plane pass, the default there: one workgroup per z plane
+ * performs the y inverse, the x pass and the y forward in its LDS, and one
+ * more the member's band step; variant 6 = variant 4 with its inputs staged
+ * pairwise through two buffers, less LDS per wave)
  * on the grid sizes and precisions of `members`, and keep the fastest
  * per (pass, n, precision) for later steps (the x pass timed in its place,
- * each launch after the y inverse that writes its inputs).  Only scratch buffers are written:
+ * each launch after the y inverse that writes its inputs, and for n <= 64
+ * with the y forward after it, against the plane pass alone).  Only scratch buffers are written:
  * member state is unchanged.  `cache_path` (may be NULL) names a text file of
  * "pass:n:precision variant" lines: entries found there are used without
  * timing, and the file is rewritten with the full table.  Synchronises. */

@@ -291,6 +291,14 @@ bool zinv_fused(const ens_ctx *ctx, int pass, int stage, int n, int prec, StepKi
     return pass == P_ZINV && variant_of(ctx, P_ZFWD, n, prec) == 1 && (stage > 0 || k.zinv0_done);
 }
 
+// Passes another launch of the stage performs: the fused z inverse, and with
+// the plane pass (an x-pass variant) the band step and the y passes.
+bool pass_done(const ens_ctx *ctx, int pass, int stage, int n, int prec, StepKind k) {
+    if ((pass == P_BAND || pass == P_YINV || pass == P_YFWD) && plane_pass(n, variant_of(ctx, P_XPASS, n, prec)))
+        return true;
+    return zinv_fused(ctx, pass, stage, n, prec, k);
+}
+
 // The variant launched for a pass: the fused z forward's last stage runs as
 // the internal variant 2 when the next step of the call takes its z inverse.
 int launch_variant(const ens_ctx *ctx, int pass, int stage, int n, int prec, StepKind k) {
@@ -303,7 +311,7 @@ hipError_t enqueue_group(const ens_ctx *ctx, const Group &g, hipStream_t s, Step
     hipError_t e;
     for (int stage = 0; stage < 3; stage++)
         for (int pass = P_BAND; pass <= P_ZFWD; pass++) {
-            if (zinv_fused(ctx, pass, stage, g.n, g.prec, k)) continue;
+            if (pass_done(ctx, pass, stage, g.n, g.prec, k)) continue;
             if ((e = launch_pass(pass, launch_variant(ctx, pass, stage, g.n, g.prec, k), g.n, g.prec, g.dev, cnt,
                                  stage, g.tw, s)))
                 return e;
@@ -351,7 +359,7 @@ hipError_t enqueue_step(const ens_ctx *ctx, const Plan &pl, hipStream_t s, Prof 
         for (const Group &g : pl.groups) {
             const int cnt = (int)g.ids.size();
             for (int pass = P_BAND; pass <= P_ZFWD; pass++) {
-                if (zinv_fused(ctx, pass, stage, g.n, g.prec, k)) continue;
+                if (pass_done(ctx, pass, stage, g.n, g.prec, k)) continue;
                 const int v = launch_variant(ctx, pass, stage, g.n, g.prec, k);
                 if ((e = rec(pass, [&] { return launch_pass(pass, v, g.n, g.prec, g.dev, cnt, stage, g.tw, s); }))) return e;
             }
@@ -1021,12 +1029,20 @@ ENS_API ens_status ens_autotune(ens_ctx *ctx, const int32_t *members, int32_t co
             // The x pass is timed in its place in the stage, each launch after
             // the y inverse (already tuned) that writes its inputs: variants
             // within a few per cent of each other in isolation rank differently
-            // there.
-            const int prev = pass == P_XPASS ? variant_of(ctx, P_YINV, g.n, g.prec) : -1;
+            // there.  Where one variant is the plane pass, which needs no y passes,
+            // the others are timed with a y forward too (the band step, which it
+            // also takes over, writes the state and is left out on both sides).
+            const bool xp = pass == P_XPASS;
+            bool plane = false;
+            for (int v = 0; v < pass_variants(pass); v++) plane = plane || (xp && plane_pass(g.n, v));
             auto launch = [&](int v) -> hipError_t {
-                if (prev >= 0)
-                    if (hipError_t e = launch_pass(P_YINV, prev, g.n, g.prec, g.dev, cnt, 1, g.tw, s)) return e;
-                return launch_pass(pass, v, g.n, g.prec, g.dev, cnt, 1, g.tw, s);
+                auto go = [&](int p, int var, int stage) { return launch_pass(p, var, g.n, g.prec, g.dev, cnt, stage, g.tw, s); };
+                if (xp && plane_pass(g.n, v)) return go(pass, v, 1 + 4);
+                if (xp)
+                    if (hipError_t e = go(P_YINV, variant_of(ctx, P_YINV, g.n, g.prec), 1)) return e;
+                if (hipError_t e = go(pass, v, 1)) return e;
+                if (!plane) return hipSuccess;
+                return go(P_YFWD, variant_of(ctx, P_YFWD, g.n, g.prec), 1);
             };
             for (int v = 0; v < pass_variants(pass); v++) {
                 for (int w = 0; w < 2; w++) HIPCK(ctx, launch(v));

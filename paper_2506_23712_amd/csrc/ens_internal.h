@@ -70,7 +70,7 @@ struct MemberDev {
     void *bufA;        // z-inverse out [5][n (z)][ZP] (planes as in uh, pad zeroed) /
                        // x-pass out [3][n / ZB][n (y)][ZB (z)][KX] (the rows of its input)
     void *bufB;        // y-inverse out [6][n / ZB][n (y)][BL = ZB (z) x KX] /
-                       // y-forward out [3][n / ZB][2K+1 (ky)][BL]
+                       // y-forward out [3][n / ZB][2K+1 (ky)][BL], for n <= 64 [3][n (z)][ZP]
                        // (statistics: [6][n][2K+1][PX] and [9][n][n][PX], PX = kx_pitch)
     DevState *st;      // diag.E: energy at the end of the last step (or of the field as set)
     double *partials;  // per-workgroup FP64 partial sums
@@ -135,6 +135,11 @@ enum Pass { P_BAND = 0, P_ZINV = 1, P_YINV = 2, P_XPASS = 3, P_YFWD = 4, P_ZFWD 
 hipError_t launch_pass(int pass, int variant, int n, int prec, const MemberDev *mem, int count, int stage,
                        const void *tw, hipStream_t s);
 int pass_variants(int pass);
+// Whether x-pass variant `variant` at grid size n is the plane pass, which also
+// performs the y inverse, the y forward and (at stage < 4; not at stage + 4)
+// the band step.
+bool plane_pass(int n, int variant);
+hipError_t launch_plane(int n, int prec, const MemberDev *mem, int count, int stage, bool band, const void *tw, hipStream_t s);
 int default_variant(int pass, int n, int prec);
 
 hipError_t launch_init_field(int n, int prec, const MemberDev *mem, uint64_t seed, double k_peak, double e0, hipStream_t s);

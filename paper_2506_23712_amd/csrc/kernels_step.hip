@@ -21,144 +21,15 @@
 #include "ens_internal.h"
 #include "fft.hpp"
 #include "gmem.hpp"
+#include "step_common.hpp"
 
 namespace ens {
 
-__device__ __forceinline__ int mode_of(int n, int N) { return n <= N / 2 ? n : n - N; }
-
-// FP64 block sum with a fixed combination order (deterministic).
-template <int NT>
-__device__ __forceinline__ double block_sum(double v, double *red) {
-    red[threadIdx.x] = v;
-    __syncthreads();
-#pragma unroll
-    for (int s = NT / 2; s > 0; s >>= 1) {
-        if ((int)threadIdx.x < s) red[threadIdx.x] += red[threadIdx.x + s];
-        __syncthreads();
-    }
-    double r = red[0];
-    __syncthreads();
-    return r;
-}
-
-// ------------------------------------------------------------ pass configs
-// E = complex values per thread (a line of N uses N/E threads).  Variants of
-// E are compiled for the pencil passes and the x pass; the host picks one per
-// (pass, N, precision) from its tuning table.
-template <typename P, int N, int E_, int TM = 1> struct Cfg {
-    static constexpr int K = N / 3, KX = K + 1;                 // x-modes kept
-    static constexpr int NZLS = (2 * K + 1) * KX;               // z-lines: modes of a z plane
-    static constexpr int ZP = state_pitch(K, (int)sizeof(Cx<P>));  // plane pitch (whole 128-byte lines)
-    static constexpr int S = (2 * K + 1) * ZP;                  // state elements per component
-    static constexpr int NYL = N * KX;                          // y-lines
-    // y-pencil buffers are blocked by z: ZB consecutive z rows (BL = ZB (K+1)
-    // lines, the fewest that fill whole 128-byte lines) are stored together,
-    // position by position, so that a pass's position stride is BL values
-    // (5.5 KB at N = 256) instead of the whole y-line count
-    static constexpr int TLB = 128 / (int)sizeof(Cx<P>);
-    static constexpr int ZB = TLB / gcd_int(KX, TLB), BL = ZB * KX;
-    // element of line L at position p of a y-pencil buffer with NP positions
-    __device__ static constexpr uint32_t yel(int L, int p, int NP) {
-        return (uint32_t)(L / BL) * (uint32_t)(NP * BL) + (uint32_t)p * BL + (uint32_t)(L % BL);
-    }
-    static constexpr int E = E_ > N ? N : E_;
-    static constexpr int M = N / E;
-    // Lines per workgroup of the y/z pencil passes: at least 256 threads and
-    // at least one 128-byte line per position (16 FP32 / 8 FP64 consecutive
-    // lines, a multiple of which is where every tile starts), so that every
-    // store covers whole lines; at most 1024 threads (512
-    // with 16 values per thread, so that a wave may use 256 VGPRs); gfx950
-    // gives a workgroup up to 160 KiB of LDS.
-    static constexpr int TL = 128 / (int)sizeof(Cx<P>);
-    static constexpr int MAXT = E >= 16 ? 512 : 1024;             // 16 values/thread: keep 256 VGPRs available
-    // TM > 1 (autotuner variants 2, 3 of the y/z passes): TM times as many
-    // lines, i.e. TM whole lines per position, where the thread budget above
-    // allows it (not for 16 FP64 values per thread, which would spill)
-    static constexpr int T1 = N <= 256 ? (256 / M > TL ? 256 / M : TL) : (TL * M <= MAXT ? TL : MAXT / M);
-    static constexpr int T = (T1 * TM * M <= MAXT && !(sizeof(P) == 8 && E >= 16)) ? T1 * TM : T1;
-    static constexpr int NT = T * M;
-    // z/y inverse passes: waves per SIMD the register budget is cut for
-    static constexpr int PMINW = (sizeof(P) == 4 && E == 16 && NT == 256) ? 3 : 1;
-    static constexpr int TX = 256 / M;                          // x pass: 256 threads
-    // z forward + update: 8 values per thread, 512 threads up to N = 256;
-    // 16 values per thread and the pencil rule above for longer lines
-    static constexpr int EZ = N <= 256 ? 8 : 16, MZ = N / EZ;
-    static constexpr int TZ = N <= 256 ? ((512 / MZ) < 1 ? 1 : 512 / MZ) : (TL * MZ <= 512 ? TL : 512 / MZ);
-    static constexpr int NTZ = TZ * MZ;
-    // z forward + update, waves per SIMD the register budget is cut for: two
-    // 512-thread workgroups per compute unit (4 waves per SIMD) in FP32; the
-    // FP64 update keeps its registers
-    static constexpr int ZMINB = (sizeof(P) == 4 && NTZ == 512 && EZ == 8) ? 4 : 1;
-};
-
 // ================================================================== band
-// One workgroup per member: the band's part of the m_x = 0 plane made
-// Hermitian, then E_f over the forcing band (FP64, fixed order).
 template <typename P>
 __global__ void __launch_bounds__(256) k_band_energy(const MemberDev *__restrict__ mems, int stage) {
     __shared__ double red[256];
-    const MemberDev &md = mems[blockIdx.x];
-    const int K = md.K;
-    const long long zp = md.zp;
-    const long long S = (long long)(2 * K + 1) * zp;
-    int B = (int)floor(sqrt(md.kf_hi2));
-    if (B > K) B = K;
-    const int W = 2 * B + 1;
-    const long long ncand = (long long)(B + 1) * W * W;
-    // The velocity is real, so the m_x = 0 plane of its half spectrum is
-    // Hermitian: u(0, -m_y, -m_z) = conj u(0, m_y, m_z).  A part breaking
-    // that is invisible to the nonlinear term, and the linear forcing would
-    // amplify it in the band; the band's part of the plane is made Hermitian
-    // here (one thread per pair) before E_f is summed.
-    for (int c = (int)threadIdx.x; c < W * W; c += 256) {
-        const int my = c % W - B, mz = c / W - B;
-        const int m2 = my * my + mz * mz;
-        if (!(mz > 0 || (mz == 0 && my > 0)) || (double)m2 < md.kf_lo2 || (double)m2 > md.kf_hi2) continue;
-        const int iy = my >= 0 ? my : my + 2 * K + 1, iz = mz;
-        const int jy = my > 0 ? 2 * K + 1 - my : -my, jz = mz > 0 ? 2 * K + 1 - mz : 0;
-        const uint32_t i1 = (uint32_t)((long long)iz * zp + (long long)iy * (K + 1));
-        const uint32_t i2 = (uint32_t)((long long)jz * zp + (long long)jy * (K + 1));
-#pragma unroll
-        for (int comp = 0; comp < 3; comp++) {
-            const Fld<P> F(md.uh, comp * S);
-            const Cx<P> a = F.ld(i1), b = F.ld(i2);
-            const Cx<P> h = {P(0.5) * (a.re + b.re), P(0.5) * (a.im - b.im)};
-            F.st(i1, h);
-            F.st(i2, {h.re, -h.im});
-        }
-    }
-    __syncthreads();
-    double acc = 0.0;
-    for (long long c = threadIdx.x; c < ncand; c += 256) {
-        const int mx = (int)(c % (B + 1));
-        const int my = (int)((c / (B + 1)) % W) - B;
-        const int mz = (int)(c / ((long long)(B + 1) * W)) - B;
-        const int m2 = mx * mx + my * my + mz * mz;
-        if (m2 == 0 || (double)m2 < md.kf_lo2 || (double)m2 > md.kf_hi2) continue;
-        const int iy = my >= 0 ? my : my + 2 * K + 1, iz = mz >= 0 ? mz : mz + 2 * K + 1;
-        const long long idx = (long long)iz * zp + (long long)iy * (K + 1) + mx;
-        const double w = mx > 0 ? 1.0 : 0.5;
-#pragma unroll
-        for (int comp = 0; comp < 3; comp++) {
-            Cx<P> v = Fld<P>(md.uh, comp * S).ld((uint32_t)idx);
-            acc += w * ((double)v.re * (double)v.re + (double)v.im * (double)v.im);
-        }
-    }
-    const double ef = block_sum<256>(acc, red);
-    if (threadIdx.x == 0) {
-        // A band holding no more than kForceEmptyFrac of the energy the field
-        // had at the start of the step (diag.E) is empty: the linear forcing,
-        // eps/(2 E_f) u, would otherwise amplify rounding-level band modes to
-        // inject eps.  Ef = 0 tells the update to add no forcing.
-        const bool forced = ef > kForceEmptyFrac * md.st->diag.E;
-        md.st->Ef = forced ? ef : 0.0;
-        if (stage == 0) {
-            md.st->diag.E_f = ef;
-            md.st->diag.inj = forced ? md.eps_m : 0.0;
-            md.st->umax_bits = 0ull;
-            if (!forced && md.eps_m != 0.0) md.st->diag.flags |= 2;
-        }
-    }
+    band_energy<P, 256>(mems[blockIdx.x], stage, red);
 }
 
 // Loads of one pencil (E values of line L at positions t + M m), truncated:
@@ -1105,7 +976,10 @@ __global__ void __launch_bounds__((Cfg<P, N, EV, TM>::NT)) k_yfwd(const MemberDe
     const bool inb = L < NYL;
     const bool valid = inb;
     const uint32_t in_base = C::yel(inb ? L : 0, 0, N);           // + y BL
-    const uint32_t out_base = C::yel(inb ? L : 0, 0, 2 * K + 1);  // + m_y BL
+    // + m_y BL (blocks of z), or + m_y (K+1) (plane by plane)
+    const int Lo = inb ? L : 0;
+    const uint32_t out_base = C::PLN ? (uint32_t)(Lo / C::KX) * C::ZP + (uint32_t)(Lo % C::KX) : C::yel(Lo, 0, 2 * K + 1);
+    constexpr uint32_t OS = C::PLN ? C::KX : C::BL;
     auto load = [&](Cx<P> *v, int f) {
         const Fld<P> in(md.bufA, f * FS);
 #pragma unroll
@@ -1118,11 +992,11 @@ __global__ void __launch_bounds__((Cfg<P, N, EV, TM>::NT)) k_yfwd(const MemberDe
         if (f < 2) load(p, f + 1);
         line_fft<P, N, E, T, -1>(a, lds, l, t, tw);
         if (inb) {
-            const Fld<P> o(md.bufB, (long long)f * (2 * K + 1) * NYL);
+            const Fld<P> o(md.bufB, (long long)f * (C::PLN ? N * C::ZP : (2 * K + 1) * NYL));
 #pragma unroll
             for (int s = 0; s < E; s++) {
                 const int my = mode_of(Plan<N, E>::out_pos(t, s), N);
-                if (my >= -K && my <= K) o.st(out_base + (uint32_t)(my >= 0 ? my : my + 2 * K + 1) * C::BL, a[s]);
+                if (my >= -K && my <= K) o.st(out_base + (uint32_t)(my >= 0 ? my : my + 2 * K + 1) * OS, a[s]);
             }
         }
         if (f < 2) {
@@ -1195,14 +1069,40 @@ __global__ void __launch_bounds__((Cfg<P, N, 8>::NTZ), (Cfg<P, N, 8>::ZMINB)) k_
     Cx<P> a[3][E];
 #pragma unroll
     for (int f = 0; f < 3; f++) {
-        const Fld<P> in(md.bufB, (long long)f * (2 * K + 1) * NYL);
+        const Fld<P> in(md.bufB, (long long)f * (C::PLN ? N * C::ZP : (2 * K + 1) * NYL));
 #pragma unroll
         for (int m = 0; m < E; m++) {
             const int z = t + M * m;
-            a[f][m] = valid ? in.ld((uint32_t)(z / ZB) * (uint32_t)((2 * K + 1) * BL) + (uint32_t)(z % ZB) * KX + Lz)
-                            : czero<P>();
+            const uint32_t at = C::PLN ? (uint32_t)(z * C::ZP + L)
+                                       : (uint32_t)(z / ZB) * (uint32_t)((2 * K + 1) * BL) + (uint32_t)(z % ZB) * KX + Lz;
+            a[f][m] = valid ? in.ld(at) : czero<P>();
         }
     }
+    const Fld<P> U[3] = {Fld<P>(md.uh, 0), Fld<P>(md.uh, S), Fld<P>(md.uh, 2 * S)};
+    const Fld<P> Q[3] = {Fld<P>(md.q, 0), Fld<P>(md.q, S), Fld<P>(md.q, 2 * S)};
+    // The state loads of HB outputs are issued together (from a valid address
+    // for a mode that is not kept, whose value is then discarded), so that their
+    // latencies overlap.  N <= 64: of all outputs, before the transforms (a
+    // member has too few waves there to hide a chain of loads; the registers
+    // are free).  Larger: pairs in stage 0, which has no RK register to read,
+    // just before their arithmetic; one at a time in stages 1 and 2 (pairs with
+    // their register loads spill).
+    constexpr bool PRE = N <= 64;
+    constexpr int HB = PRE ? E : (stage == 0 ? 2 : 1);
+    Cx<P> ub[HB][3], qb[HB][3];
+    auto load_state = [&](int s0) {
+#pragma unroll
+        for (int j = 0; j < HB; j++) {
+            const int mz = mode_of(Plan<N, E>::out_pos(t, s0 + j), N);
+            const bool keep = mz >= -K && mz <= K;
+            const uint32_t idx = (uint32_t)(keep ? (mz >= 0 ? mz : mz + 2 * K + 1) : 0) * C::ZP + (valid ? L : 0);
+#pragma unroll
+            for (int c = 0; c < 3; c++) ub[j][c] = U[c].ld(idx);
+#pragma unroll
+            for (int c = 0; c < 3; c++) qb[j][c] = stage == 0 ? czero<P>() : Q[c].ld(idx);
+        }
+    };
+    if constexpr (PRE) load_state(0);
 #pragma unroll
     for (int f = 0; f < 3; f++) line_fft<P, N, E, T, -1>(a[f], lds, l, t, tw);
     __syncthreads();
@@ -1210,29 +1110,11 @@ __global__ void __launch_bounds__((Cfg<P, N, 8>::NTZ), (Cfg<P, N, 8>::ZMINB)) k_
     const P dk = (P)md.dk, nu = (P)md.nu;
     const double kf_lo2 = md.kf_lo2, kf_hi2 = md.kf_hi2;
     const bool explicit_visc = md.visc_mode == 1;
-    const Fld<P> U[3] = {Fld<P>(md.uh, 0), Fld<P>(md.uh, S), Fld<P>(md.uh, 2 * S)};
-    const Fld<P> Q[3] = {Fld<P>(md.q, 0), Fld<P>(md.q, S), Fld<P>(md.q, 2 * S)};
     double eacc = 0.0, dacc = 0.0;
     if (valid) {
-        // stage 0 (no RK register to read) takes the outputs in pairs: the
-        // state loads of a pair are issued before its arithmetic (from a
-        // valid address for a mode that is not kept, whose value is then
-        // discarded), so that their latencies overlap; stages 1 and 2 take
-        // one output at a time (pairs with their register loads spill)
-        constexpr int HB = stage == 0 ? 2 : 1;
 #pragma unroll
         for (int s0 = 0; s0 < E; s0 += HB) {
-            Cx<P> ub[HB][3], qb[HB][3];
-#pragma unroll
-            for (int j = 0; j < HB; j++) {
-                const int mz = mode_of(Plan<N, E>::out_pos(t, s0 + j), N);
-                const bool keep = mz >= -K && mz <= K;
-                const uint32_t idx = (uint32_t)(keep ? (mz >= 0 ? mz : mz + 2 * K + 1) : 0) * C::ZP + L;
-#pragma unroll
-                for (int c = 0; c < 3; c++) ub[j][c] = U[c].ld(idx);
-#pragma unroll
-                for (int c = 0; c < 3; c++) qb[j][c] = stage == 0 ? czero<P>() : Q[c].ld(idx);
-            }
+            if constexpr (!PRE) load_state(s0);
 #pragma unroll
             for (int j = 0; j < HB; j++) {
                 const int s = s0 + j;
@@ -1362,6 +1244,7 @@ __global__ void __launch_bounds__(256) k_end_step(const MemberDev *__restrict__ 
         st->diag.rlambda = (D > 0.0 && md.nu > 0.0) ? (2.0 * E / 3.0) * sqrt(15.0 / (md.nu * D)) : 0.0;
         st->diag.kmax_eta = D > 0.0 ? md.K * md.dk * pow(md.nu * md.nu * md.nu / D, 0.25) : 0.0;
         st->diag.step += 1;
+        st->umax_bits = 0ull;                // for the next step's x pass (which may run beside its band step)
         if (!isfinite(E)) st->diag.flags |= 1;
     }
 }
@@ -1455,6 +1338,11 @@ static hipError_t run_pass(int pass, int variant, const MemberDev *mem, int coun
             else if constexpr (N >= 64) return run_xpass_dma<P, N, 8>(mem, count, stage, twp, s);
             else return run_pencil<P, N, 8>(pass, mem, count, stage, twp, s);
         }
+        if (pass == P_XPASS && variant == 5) {
+            // the plane pass where it exists; stage + 4: without the band step
+            if constexpr (plane_ok(N))
+                return launch_plane(N, sizeof(P) == 4 ? ENS_FP32 : ENS_FP64, mem, count, stage & 3, stage < 4, tw, s);
+        }
         if (pass == P_XPASS && (variant == 4 || variant == 5)) {
             // wave-private: 16 (FP32) / 8 (FP64) values per thread, or half that
             // (where that tile shape is invalid: the streamed x pass, variant 2)
@@ -1462,7 +1350,7 @@ static hipError_t run_pass(int pass, int variant, const MemberDev *mem, int coun
             if constexpr (N >= 64) {
                 if constexpr (xwave_ok(N, EA, CS))
                     if (variant == 4) return run_xpass_wave<P, N, EA>(mem, count, stage, twp, s);
-                if constexpr (xwave_ok(N, EB, CS))
+                if constexpr (xwave_ok(N, EB, CS) && !plane_ok(N))
                     if (variant == 5) return run_xpass_wave<P, N, EB>(mem, count, stage, twp, s);
                 return run_xpass_dma<P, N, 8>(mem, count, stage, twp, s);
             } else return run_pencil<P, N, 8>(pass, mem, count, stage, twp, s);
@@ -1534,13 +1422,15 @@ int pass_variants(int pass) {
 }
 
 int default_variant(int pass, int n, int prec) {
-    if (pass == P_XPASS) return n >= 64 ? 2 : 0;               // streamed, 8 values per thread
+    if (pass == P_XPASS) return plane_ok(n) ? 5 : 2;           // plane pass; streamed, 8 values per thread
     if (pass == P_ZINV || pass == P_YINV || pass == P_YFWD) return prec == ENS_FP32 ? 1 : 0;
     // fused z forward: 0.4-1.8 % faster per step up to n = 512 (both
     // precisions); at n = 1024 its registers spill and it gains nothing
     if (pass == P_ZFWD) return n <= 512 ? 1 : 0;
     return 0;
 }
+
+bool plane_pass(int n, int variant) { return plane_ok(n) && variant == 5; }
 
 long long zfwd_blocks(int n, int prec) {
     auto blocks = [](auto cfg) { using C = decltype(cfg); return (long long)((C::NZLS + C::TZ - 1) / C::TZ); };

@@ -29,7 +29,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 
 
 # sources of the time-step kernels whose traffic the summaries record
-STEP_SOURCES = ("kernels_step.hip", "fft.hpp", "gmem.hpp", "ens_internal.h")
+STEP_SOURCES = ("kernels_step.hip", "kernels_plane.hip", "step_common.hpp", "fft.hpp", "gmem.hpp", "ens_internal.h")
 
 
 def source_hash() -> str:
@@ -82,6 +82,8 @@ def kernel_name(pass_name: str, n: int, prec: str, variant) -> str:
     if pass_name == "zfwd_update":                             # the kernel of the middle RK stage
         return f"ens::k_zfwd_update<{p}, {n}, 1, {'true' if variant == 1 else 'false'}>"
     ea = 16 if prec == "fp32" else 8
+    if pass_name == "xpass" and variant == 5 and n <= 64:       # the plane pass (y inverse, x pass, y forward)
+        return f"ens::k_plane<{p}, {n}>"
     if pass_name == "xpass" and variant == 6 and n >= 64:
         return f"ens::k_xpass_wave2<{p}, {n}, {ea}>"
     if pass_name == "xpass" and variant in (4, 5) and n >= 64:
