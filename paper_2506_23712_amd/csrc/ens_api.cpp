@@ -680,10 +680,15 @@ ENS_API ens_status ens_get_stats(ens_ctx *ctx, int32_t mid, uint64_t *counts, do
     if (moments) HIPCK(ctx, hipMemcpy(moments, m->md.moments, ENS_NMOM * sizeof(double), hipMemcpyDeviceToHost));
     if (n_points) {
         // every snapshot adds n^3 samples to the QR histogram (bins + specials)
-        std::vector<uint64_t> c(ctx->hg.n_counts);
-        HIPCK(ctx, hipMemcpy(c.data(), m->md.counts, c.size() * sizeof(uint64_t), hipMemcpyDeviceToHost));
+        std::vector<uint64_t> c;
+        const uint64_t *q = counts;            // already on the host where the caller takes the counters
+        if (!q) {
+            c.resize(ctx->hg.off_le);
+            HIPCK(ctx, hipMemcpy(c.data(), m->md.counts, c.size() * sizeof(uint64_t), hipMemcpyDeviceToHost));
+            q = c.data();
+        }
         uint64_t s = 0;
-        for (long long i = 0; i < ctx->hg.off_le; i++) s += c[i];
+        for (long long i = 0; i < ctx->hg.off_le; i++) s += q[i];
         *n_points = s;
     }
     return ENS_OK;

@@ -317,49 +317,36 @@ __global__ void __launch_bounds__(256, 2) k_gxstats(const MemberDev *__restrict_
             }
         }
     };
-    // FP32 only: in FP64 the second pair of registers would spill
-    constexpr bool PF = sizeof(P) == 4;
+    // Each pair is loaded one pair ahead; across tiles in FP32 only: in FP64 the
+    // second pair of registers fits beside the transforms, not beside the
+    // pointwise work.  (FP64 without it: 577 us for seven members of 128^3,
+    // with it 526 us.)
+    constexpr bool PFX = sizeof(P) == 4;
     Cx<P> ra[E], rb[E];
-    if (PF && (int)blockIdx.x < ntiles) load_pair(blockIdx.x, 0, ra, rb);
+    if (PFX && (int)blockIdx.x < ntiles) load_pair(blockIdx.x, 0, ra, rb);
     for (int tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
         P g[9][E];
         Cx<P> v[E];
+        if (!PFX) load_pair(tile, 0, ra, rb);
 #pragma unroll
         for (int pr = 0; pr < 5; pr++) {
             const int fa = 2 * pr, fb = 2 * pr + 1;
-            if constexpr (PF) {
-                Cx<P> ca[E], cb[E];
+            Cx<P> ca[E], cb[E];
 #pragma unroll
-                for (int m = 0; m < E; m++) { ca[m] = ra[m]; cb[m] = rb[m]; }
-                if (pr < 4) load_pair(tile, pr + 1, ra, rb);
-                else if (tile + (int)gridDim.x < ntiles) load_pair(tile + gridDim.x, 0, ra, rb);
+            for (int m = 0; m < E; m++) { ca[m] = ra[m]; cb[m] = rb[m]; }
+            if (pr < 4) load_pair(tile, pr + 1, ra, rb);
+            else if (PFX && tile + (int)gridDim.x < ntiles) load_pair(tile + gridDim.x, 0, ra, rb);
 #pragma unroll
-                for (int m = 0; m < E; m++) {
-                    const int n = t + M * m;
-                    const bool lo = n <= K, hi = n >= N - K;
-                    const P kx = (P)(lo ? n : N - n);
-                    Cx<P> A = ca[m], B = cb[m];
-                    if (fa % 3 == 0) A = mul_i(cscale(A, dk * kx));
-                    if (fb < 9 && fb % 3 == 0) B = mul_i(cscale(B, dk * kx));
-                    if (hi && !lo) { A = cconj(A); B = cconj(B); }
-                    if (n == 0) { A.im = P(0); B.im = P(0); }
-                    v[m] = {A.re - B.im, A.im + B.re};
-                }
-            } else {
-                const uint32_t rbase = (uint32_t)(tile * T + l) * PX;
-                auto spec = [&](int f, uint32_t kx) -> Cx<P> {
-                    const Cx<P> x = Fld<P>(md.bufB, foff(f)).ld(rbase + kx);
-                    return f % 3 == 0 ? mul_i(cscale(x, dk * (P)kx)) : x;
-                };
-#pragma unroll
-                for (int m = 0; m < E; m++) {
-                    const int n = t + M * m;
-                    Cx<P> A = czero<P>(), B = czero<P>();
-                    if (n <= K) { A = spec(fa, n); if (fb < 9) B = spec(fb, n); }
-                    else if (n >= N - K) { A = cconj(spec(fa, N - n)); if (fb < 9) B = cconj(spec(fb, N - n)); }
-                    if (n == 0) { A.im = P(0); B.im = P(0); }
-                    v[m] = {A.re - B.im, A.im + B.re};
-                }
+            for (int m = 0; m < E; m++) {
+                const int n = t + M * m;
+                const bool lo = n <= K, hi = n >= N - K;
+                const P kx = (P)(lo ? n : N - n);
+                Cx<P> A = ca[m], B = cb[m];
+                if (fa % 3 == 0) A = mul_i(cscale(A, dk * kx));
+                if (fb < 9 && fb % 3 == 0) B = mul_i(cscale(B, dk * kx));
+                if (hi && !lo) { A = cconj(A); B = cconj(B); }
+                if (n == 0) { A.im = P(0); B.im = P(0); }
+                v[m] = {A.re - B.im, A.im + B.re};
             }
             line_fft<P, N, E, T, +1, WP ? 2 : 0, LY>(v, lds, l, t, tw);
 #pragma unroll
@@ -489,21 +476,24 @@ __global__ void __launch_bounds__(256, 2) k_gxstats(const MemberDev *__restrict_
     }
 }
 
-// one workgroup per member: moments += sum over blocks (fixed order)
-__global__ void __launch_bounds__(256) k_stats_reduce(const MemberDev *__restrict__ mems, long long nblocks) {
-    __shared__ double red[256];
+// One workgroup per member: moments += sum over blocks.  Thread (g, i) adds sum
+// i of every 32nd block, in order, and the 32 group sums are added in order
+// (deterministic); a row of partials is one 256-byte read.  One reduction tree
+// after another over the 26 sums took 34 us, this 6 us.
+__global__ void __launch_bounds__(1024) k_stats_reduce(const MemberDev *__restrict__ mems, long long nblocks) {
+    __shared__ double red[32][33];
     const MemberDev &md = mems[blockIdx.x];
-    for (int i = 0; i < 26; i++) {
-        double x = 0.0;
-        for (long long b = threadIdx.x; b < nblocks; b += 256) x += md.partials[b * 32 + i];
-        red[threadIdx.x] = x;
-        __syncthreads();
-        for (int s = 128; s > 0; s >>= 1) {
-            if ((int)threadIdx.x < s) red[threadIdx.x] += red[threadIdx.x + s];
-            __syncthreads();
-        }
-        if (threadIdx.x == 0) md.moments[i] += red[0];
-        __syncthreads();
+    const int i = threadIdx.x & 31, g = threadIdx.x >> 5;
+    double x = 0.0;
+#pragma unroll 4
+    for (long long b = g; b < nblocks; b += 32) x += md.partials[b * 32 + i];
+    red[g][i] = x;
+    __syncthreads();
+    if (threadIdx.x < 26) {
+        double sum = 0.0;
+#pragma unroll
+        for (int k = 0; k < 32; k++) sum += red[k][threadIdx.x];
+        md.moments[threadIdx.x] += sum;
     }
     // snapshot sums of the member's energy and dissipation (its last step's
     // values, those of the field this snapshot sees) and the snapshot count
@@ -574,7 +564,7 @@ static hipError_t stats_pass(int pass, const MemberDev *mem, int count, const en
         const int per = xstats_grid(N, count);
         k_gxstats<P, N, EX><<<dim3(per, count), 256, dyn, s>>>(mem, twp, h);
     } else {
-        k_stats_reduce<<<count, 256, 0, s>>>(mem, (long long)xstats_grid(N, count));
+        k_stats_reduce<<<count, 1024, 0, s>>>(mem, (long long)xstats_grid(N, count));
     }
     return hipGetLastError();
 }

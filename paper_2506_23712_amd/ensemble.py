@@ -120,8 +120,8 @@ class Member:
         """(counts uint64 tensor, moments float64 tensor, grid points summed)."""
         n = ctypes.c_size_t()
         check(lib().ens_stats_len(self.ens.ctx, ctypes.byref(n)))
-        counts = torch.zeros(n.value, dtype=torch.int64)
-        mom = torch.zeros(_lib.ENS_NMOM, dtype=torch.float64)
+        counts = torch.empty(n.value, dtype=torch.int64)
+        mom = torch.empty(_lib.ENS_NMOM, dtype=torch.float64)
         npts = ctypes.c_uint64()
         check(lib().ens_get_stats(self.ens.ctx, self.id,
                                   ctypes.cast(counts.data_ptr(), ctypes.POINTER(ctypes.c_uint64)),
