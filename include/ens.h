@@ -202,13 +202,12 @@ ens_status ens_get_diag(ens_ctx *ctx, int32_t m, ens_diag *out);
  * variant 2 = persistent workgroups streaming their inputs by
  * direct-to-LDS loads, 8 values per thread, the same as variant 0 for n < 64;
  * variant 3 = the same with 16 values per thread for FP32 and 128 <= n <= 512,
- * else variant 2; variants 4 and 5 = the streamed pass with one wave per
- * workgroup and every transform exchange inside the wave, 16 or 8 (FP32) /
- * 8 or 4 (FP64) values per thread, n >= 64, else variant 2 - but for n <= 64
- * variant 5 is the plane pass, the default there: one workgroup per z plane
- * performs the y inverse, the x pass and the y forward in its LDS, and one
- * more the member's band step; variant 6 = variant 4 with its inputs staged
- * pairwise through two buffers, less LDS per wave)
+ * else variant 2; variant 6 = the streamed pass with one wave per
+ * workgroup, every transform exchange inside the wave and the inputs staged
+ * pairwise, 16 (FP32) / 8 (FP64) values per thread, n >= 64, else variant 2;
+ * variant 4 = variant 6; variant 5 = for n <= 64 the plane pass, the default
+ * there (one workgroup per z plane performs the y inverse, the x pass and the
+ * y forward in its LDS, and one more the member's band step), else variant 6)
  * on the grid sizes and precisions of `members`, and keep the fastest
  * per (pass, n, precision) for later steps (the x pass timed in its place,
  * each launch after the y inverse that writes its inputs, and for n <= 64

@@ -1050,6 +1050,7 @@ ENS_API ens_status ens_autotune(ens_ctx *ctx, const int32_t *members, int32_t co
                 return go(P_YFWD, variant_of(ctx, P_YFWD, g.n, g.prec), 1);
             };
             for (int v = 0; v < pass_variants(pass); v++) {
+                if (!variant_distinct(pass, g.n, v)) continue;
                 for (int w = 0; w < 2; w++) HIPCK(ctx, launch(v));
                 float v_ms = 1e30f;
                 for (int trial = 0; trial < 3; trial++) {
@@ -1073,7 +1074,7 @@ ENS_API ens_status ens_autotune(ens_ctx *ctx, const int32_t *members, int32_t co
     drop_graphs(ctx);
     if (cache_path) {
         std::ofstream f(cache_path);
-        f << "# libensdns kernel variants (pass:n:precision variant); 0 = 8, 1 = 16 values per thread, 2 and 3 = the same with twice the lines per workgroup (y/z passes) or the streamed x pass with 8 and 16, 4 to 6 = wave-private streamed x pass\n";
+        f << "# libensdns kernel variants (pass:n:precision variant); 0 = 8, 1 = 16 values per thread, 2 and 3 = the same with twice the lines per workgroup (y/z passes) or the streamed x pass with 8 and 16, 4 and 6 = wave-private streamed x pass, 5 = plane pass (n <= 64, else as 6)\n";
         for (auto &kv : cache) f << kv.first << " " << kv.second << "\n";
     }
     return ENS_OK;

@@ -128,13 +128,14 @@ enum Pass { P_BAND = 0, P_ZINV = 1, P_YINV = 2, P_XPASS = 3, P_YFWD = 4, P_ZFWD 
 // `count` MemberDev of one size n and precision; grids cover all of them.
 // `variant` selects a compiled kernel variant (0: 8 values per thread,
 // 1: 16 values per thread; y/z passes 2, 3: the same with twice the lines
-// per workgroup; x pass 2 to 6: the streamed and wave-private passes, see
+// per workgroup; x pass 2 to 6: the streamed, wave-private and plane passes, see
 // ens_autotune in ens.h; z forward 1: fused with the next stage's z inverse,
 // 2 (not selectable by callers): the last stage too, for a step followed by
 // another in the same call) for passes with pass_variants(pass) > 1.
 hipError_t launch_pass(int pass, int variant, int n, int prec, const MemberDev *mem, int count, int stage,
                        const void *tw, hipStream_t s);
 int pass_variants(int pass);
+bool variant_distinct(int pass, int n, int variant);   // false: the kernel of another variant (not timed)
 // Whether x-pass variant `variant` at grid size n is the plane pass, which also
 // performs the y inverse, the y forward and (at stage < 4; not at stage + 4)
 // the band step.

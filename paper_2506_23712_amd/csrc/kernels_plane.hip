@@ -41,6 +41,10 @@ template <typename P, int N> struct PlaneCfg {
     static constexpr int NT = N == 64 ? 512 : N == 32 ? 320 : 192, G = NT / M;
     static constexpr int MINW = N == 64 ? (sizeof(P) == 4 ? 4 : 2) : 1;   // waves per SIMD
     static constexpr int RPW = 64 / M;                         // columns of a wave in phase 2
+    // FP64: each thread's twiddles in registers (a table in LDS is read at
+    // strides that share banks, and the LDS is what bounds FP64); FP32: in LDS
+    // (its registers are what bound the workgroups per compute unit)
+    static constexpr bool REGTW = sizeof(P) == 8;
     static constexpr int NB = NT >= 256 ? 256 : 128;           // threads of the band step
     __device__ static __forceinline__ int sw(int p) { return p ^ ((p >> 3) & 7); }
     struct Row {                                               // exchange inside row l
@@ -60,7 +64,12 @@ __global__ void __launch_bounds__((PlaneCfg<P, N>::NT), (PlaneCfg<P, N>::MINW)) 
     constexpr int E = C::E, M = C::M, K = C::K, KX = C::KX, NT = C::NT, ZP = Cfg<P, N, 8>::ZP;
     constexpr unsigned ZM = truncated_slots(N, E, K);
     __shared__ __attribute__((aligned(16))) LdsT<P> pl[C::ROWS * C::PITCH];
-    __shared__ Cx<P> tw[twiddle_span(N, E)];
+    __shared__ Cx<P> twl[C::REGTW ? 1 : twiddle_span(N, E)];
+    TwRegs<P, N, E> twr;
+    const auto &tw = [&]() -> const auto & {
+        if constexpr (C::REGTW) return twr;
+        else return twl;
+    }();
     unsigned tile, mem_i;
     xcd_tile(tile, mem_i);
     const MemberDev &md = mems[mem_i];
@@ -70,7 +79,8 @@ __global__ void __launch_bounds__((PlaneCfg<P, N>::NT), (PlaneCfg<P, N>::MINW)) 
     }
     const int z = (int)tile, tid = (int)threadIdx.x;
     const P dk = (P)md.dk;
-    for (int i = tid; i < twiddle_span(N, E); i += NT) tw[i] = twg[i];
+    if constexpr (C::REGTW) twr.load(twg, tid % M);
+    else for (int i = tid; i < twiddle_span(N, E); i += NT) twl[i] = twg[i];
     // ---- phase 1: y inverse of row r = (f, kx), f = u_x, u_y, u_z, omega_x, omega_y, omega_z
     {
         const int t = tid % M;
@@ -113,7 +123,7 @@ __global__ void __launch_bounds__((PlaneCfg<P, N>::NT), (PlaneCfg<P, N>::MINW)) 
         Cx<P> v[PR][E];
 #pragma unroll
         for (int rd = 0; rd < PR; rd++) load(v[rd], rd);
-        __syncthreads();                                       // twiddles
+        if constexpr (!C::REGTW) __syncthreads();              // twiddles
 #pragma unroll
         for (int rd = 0; rd < RD; rd++) {
             if (rd >= PR) load(v[rd % PR], rd);
@@ -125,6 +135,7 @@ __global__ void __launch_bounds__((PlaneCfg<P, N>::NT), (PlaneCfg<P, N>::MINW)) 
     {
         const int lane = tid & 63, wave = tid >> 6;
         const int y = wave * C::RPW + lane % C::RPW, t = lane / C::RPW;
+        if constexpr (C::REGTW) twr.load(twg, t);
         if (y < N) {                                           // whole waves
             // packed two-for-one spectrum of fields 2 pr, 2 pr + 1: C = A + i B, Hermitian fill
             auto gather = [&](Cx<P> *v, int pr) {
@@ -220,6 +231,7 @@ __global__ void __launch_bounds__((PlaneCfg<P, N>::NT), (PlaneCfg<P, N>::MINW)) 
     LdsT<P> *stg = pl + 3 * KX * C::PITCH;
     {
         const int t = tid % M;
+        if constexpr (C::REGTW) twr.load(twg, t);
         for (int r = tid / M; r < 3 * KX; r += C::G) {
             Cx<P> v[E];
 #pragma unroll

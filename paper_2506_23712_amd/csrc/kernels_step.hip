@@ -562,16 +562,27 @@ __global__ void __launch_bounds__((XCfg<P, N, EV>::NTH), (XCfg<P, N, EV>::MINB))
 // its own inputs (direct-to-LDS) and stores its own outputs, so the only
 // waits left are the exact vector-memory counts of the copies and an LDS wait
 // before a staging buffer is handed back to the copies.
-// Whether the wave-private x pass has a valid tile for (N, E, complex size):
-// a line within one wave, whole 16-byte vectors per output tile, at least one
-// wave-sized copy per field and a vector-memory count that fits its counter.
+// The six input fields are staged as three pairs through two buffers of two
+// fields each: pair q of the wave's sequence (3 per tile) goes to buffer q mod
+// 2 and is requested as soon as pair q - 2 has been read from it, so two pairs
+// are resident or in flight at any time.  A third less staging LDS per wave
+// than two buffers of three fields (19.3 against 24.8 KB for 256-point FP32
+// rows), so that eight one-wave workgroups share a compute unit, two per SIMD,
+// where six leave two SIMDs with a single wave.  Twiddles in registers in both
+// precisions: as a table in LDS, FP64 read 13 of them per 32 exchanged values,
+// at strides that share banks, and the table kept an eighth wave off the
+// compute unit (LDS active 70 % of the pass; 219 -> 208 us for one 256^3
+// member without it).
+// Whether the pass has a valid tile for (N, E, complex size): a line within
+// one wave, whole 16-byte vectors per output tile, at least one wave-sized
+// copy per field and a vector-memory count that fits its counter.
 constexpr bool xwave_ok(int N, int E, int CS) {
     const int M = N / (E > N ? N : E), K = N / 3, CPV = 16 / CS;
     if (M > 64 || 64 % M != 0) return false;
     const int R = 64 / M, RWO = R * (K + 1), RV = RWO / CPV;
     if (RWO % CPV != 0 || RV < 64) return false;
-    const int D3 = 3 * ((RV + 63) / 64), S = 3 * ((RWO / CPV + 63) / 64);
-    return D3 + S < 64;
+    const int D2 = 2 * ((RV + 63) / 64), S = 3 * ((RWO / CPV + 63) / 64);
+    return D2 + S < 64;
 }
 
 template <typename P, int N, int E_> struct XWCfg {
@@ -579,56 +590,60 @@ template <typename P, int N, int E_> struct XWCfg {
     static constexpr int R = 64 / M;                           // rows per tile (one wave)
     static constexpr int CS = (int)sizeof(Cx<P>), CPV = 16 / CS;
     static constexpr int RQ = K + 1;                           // row pitch in HBM and in the LDS staging
-    static constexpr bool REGTW = sizeof(P) == 4;               // FP32: twiddles in registers
-    static constexpr int NTW = REGTW ? 1 : twiddle_span(N, E);
     static constexpr int RW = R * RQ, RV = RW / CPV;            // a tile's elements / 16-byte vectors per field
     static constexpr int RWO = R * (K + 1), RVO = RWO / CPV;
-    static constexpr int D3 = dma_tile_ops<3, RV, 64>();          // copies per staging buffer
+    static constexpr int D2 = dma_tile_ops<2, RV, 64>();          // copies per pair
     static constexpr int S = dma_tile_ops<3, RVO, 64>();          // 16-byte stores per tile
     static constexpr int XL = N * R > 3 * RWO ? N * R : 3 * RWO;
     static constexpr int TILES = N * N / R;
-    static constexpr long long LDS_BYTES = (6LL * RW + XL + NTW) * CS + 64;
+    static constexpr long long LDS_BYTES = (4LL * RW + XL) * CS + 64;
     // waves per SIMD the register budget is cut for: what the LDS allows (one
     // wave per workgroup, four SIMDs per compute unit), at most 4
     static constexpr int WPS = (int)(163840 / ((LDS_BYTES + 511) / 512 * 512)) / 4;
     static constexpr int MINW = WPS < 1 ? 1 : (WPS > 4 ? 4 : WPS);
     static_assert(M <= 64 && 64 % M == 0, "a line must fit one wave");
-    static_assert(RW % CPV == 0 && RWO % CPV == 0 && RV >= 64 && RVO >= 64 && D3 + S < 64, "x-pass tile shape");
+    static_assert(RW % CPV == 0 && RWO % CPV == 0 && RV >= 64 && RVO >= 64 && D2 + S < 64, "x-pass tile shape");
 };
 
 template <typename P, int N, int EV>
-__global__ void __launch_bounds__(64, (XWCfg<P, N, EV>::MINW)) k_xpass_wave(const MemberDev *__restrict__ mems, const Cx<P> *__restrict__ tw, int stage) {
+__global__ void __launch_bounds__(64, (XWCfg<P, N, EV>::MINW)) k_xpass_wave2(const MemberDev *__restrict__ mems, int count, const Cx<P> *__restrict__ tw, int stage) {
     using C = XWCfg<P, N, EV>;
     using LY = WaveLay<P, N>;
     constexpr int E = C::E, M = C::M, R = C::R, K = C::K, RW = C::RW, RQ = C::RQ;
-    constexpr int RWO = C::RWO, RVO = C::RVO;
+    constexpr int RWO = C::RWO, RVO = C::RVO, D2 = C::D2, S = C::S;
     constexpr long long FSB = (long long)N * N * RQ * C::CS;         // bytes per input field
     constexpr long long FSBO = (long long)N * N * (K + 1) * C::CS;   // bytes per output field
-    __shared__ __attribute__((aligned(16))) LdsT<P> slot0[3 * RW];
-    __shared__ __attribute__((aligned(16))) LdsT<P> slot1[3 * RW];
+    __shared__ __attribute__((aligned(16))) LdsT<P> slotA[2 * RW];
+    __shared__ __attribute__((aligned(16))) LdsT<P> slotB[2 * RW];
     __shared__ __attribute__((aligned(16))) LdsT<P> lds[C::XL];
-    __shared__ Cx<P> twl[C::NTW];
-    unsigned chunk, mem_i;
-    xcd_tile(chunk, mem_i);
-    const MemberDev &md = mems[mem_i];
-    const int t0 = (int)((long long)chunk * C::TILES / gridDim.x);
-    const int t1 = (int)((long long)(chunk + 1) * C::TILES / gridDim.x);
-    if (t0 >= t1) return;                                     // uniform over the wave
-    const int t = (int)threadIdx.x % M, l = (int)threadIdx.x / M;
-    TwRegs<P, N, E> twr;
-    if constexpr (C::REGTW) twr.load(tw, t);
-    else for (int i = (int)threadIdx.x; i < C::NTW; i += 64) twl[i] = tw[i];
-    wave_fence();
-    const auto &twx = [&]() -> const auto & {
-        if constexpr (C::REGTW) return twr;
-        else return twl;
-    }();
-    const char *inb = (const char *)md.bufB;
-    char *outb = (char *)md.bufA;
-    auto request = [&](LdsT<P> *dst, int tile, int f0) {      // fields f0..f0+2 of the tile's R rows
-        dma_tile<3, C::RV, 64>(dst, inb + (long long)f0 * FSB + (long long)tile * RW * C::CS, FSB);
+    // The tiles of all members, in the order the y inverse wrote them, are cut
+    // into one range per XCD (the ranges the y passes give it, xcd_tile), and
+    // the XCD's waves walk their range side by side from its end: what the y
+    // inverse wrote last is still in the 256 MB Infinity Cache and is read
+    // first, and the y forward, which starts at the range's other end, in turn
+    // begins with what this pass wrote last.  Waves walking far apart (a
+    // contiguous range of tiles each) were slower at every size: 208 -> 195 us
+    // for one 256^3 FP64 member, 379 -> 357 for 16 of 128^3, 535 -> 508 for six
+    // 256^3 FP32 members (4.8 TB/s).
+    const int xcd = (int)(blockIdx.x & 7u), nw = ((int)gridDim.x - xcd + 7) >> 3;
+    const long long TT = (long long)count * C::TILES;
+    const int lo = (int)(xcd * TT >> 3), hi = (int)((xcd + 1) * TT >> 3);
+    int f = hi - 1 - (int)(blockIdx.x >> 3);
+    if (f < lo) return;                                       // uniform over the wave
+    // base addresses of flat tile f's member and its tile there
+    struct At { const char *in; char *out; int mem, tile; };
+    auto at = [&](int f) -> At {
+        const int m = f / C::TILES;
+        return {(const char *)mems[m].bufB, (char *)mems[m].bufA, m, f - m * C::TILES};
     };
-    // packed two-for-one spectrum of fields (fa, fb), as in the streamed x pass
+    At cur = at(f);
+    const int t = (int)threadIdx.x % M, l = (int)threadIdx.x / M;
+    TwRegs<P, N, E> twx;
+    twx.load(tw, t);
+    auto slot = [&](int i) -> LdsT<P> * { return i ? slotB : slotA; };
+    auto request = [&](LdsT<P> *dst, const At &a, int pair) {  // fields 2 pair, 2 pair + 1 of the tile's R rows
+        dma_tile<2, C::RV, 64>(dst, a.in + (long long)(2 * pair) * FSB + (long long)a.tile * RW * C::CS, FSB);
+    };
     auto gather = [&](Cx<P> *v, const LdsT<P> *fa, const LdsT<P> *fb) {
 #pragma unroll
         for (int m = 0; m < E; m++) {
@@ -657,224 +672,47 @@ __global__ void __launch_bounds__(64, (XWCfg<P, N, EV>::MINW)) k_xpass_wave(cons
     Cx<P> v[E];
     typedef float F4 __attribute__((ext_vector_type(4)));
     const unsigned lane16 = (threadIdx.x & 63u) * 16u;
-    // the tile's outputs staged in lds ([3][R][K+1], contiguous in the output)
-    // leave in wave-sized chunks of 64 vectors, the last chunk of a field moved
-    // back onto its end
-    auto store_tile = [&](int tile, bool zero) {
+    auto store_tile = [&](const At &a, bool zero) {
         constexpr int NCF = (RVO + 63) / 64, NCH = 3 * NCF;
 #pragma unroll
         for (int c = 0; c < NCH; c++) {
-            const int f = c / NCF, q = c - f * NCF;
+            const int fld = c / NCF, q = c - fld * NCF;
             const int st = q * 64 < RVO - 64 ? q * 64 : RVO - 64;
-            const F4 x = zero ? F4{0.f, 0.f, 0.f, 0.f} : *(const F4 *)((const char *)lds + (f * RVO + st) * 16 + lane16);
-            ENS_GLOBAL char *dst = (ENS_GLOBAL char *)outb + f * FSBO + (long long)tile * RWO * C::CS + st * 16;
+            const F4 x = zero ? F4{0.f, 0.f, 0.f, 0.f} : *(const F4 *)((const char *)lds + (fld * RVO + st) * 16 + lane16);
+            ENS_GLOBAL char *dst = (ENS_GLOBAL char *)a.out + fld * FSBO + (long long)a.tile * RWO * C::CS + st * 16;
             *(ENS_GLOBAL F4 *)(dst + lane16) = x;
         }
     };
-    static_assert(C::S == 3 * ((RVO + 63) / 64), "store count");
-    // Wait accounting as in the streamed x pass (vector-memory operations
-    // complete in issue order; requests are unconditional, the prologue writes
-    // zeros to the first tile's output to reproduce the loop's order).
-    request(slot0, t0, 0);
-    request(slot1, t0, 3);
-    store_tile(t0, true);
-    wait_vm<C::D3 + C::S>();                                   // fields 0-2 of the first tile
+    // Wait accounting (vector-memory operations complete in issue order).  The
+    // wave's pair requests R(q), q = 3 u + j for its u-th tile, and its tile stores
+    // S(tile) are issued in the order ... R(3u+1) S(u-1) R(3u+2) R(3u+3) R(3u+4)
+    // S(u) ..., so before reading pair 0 of tile u at most D2 + S operations
+    // issued after it may be outstanding, before pair 1 S + D2, before pair 2
+    // D2.  The prologue writes zeros to the first tile's output to reproduce
+    // that order; requests past the last tile repeat the last tile's pairs.
+    request(slot(0), cur, 0);
+    request(slot(1), cur, 1);
+    store_tile(cur, true);
+    wait_vm<D2 + S>();                                         // pair 0 of the first tile
     wave_fence();
-    gather(v, slot0, slot0 + RW);
-    for (int tile = t0; tile < t1; tile++) {
-        const bool more = tile + 1 < t1;
-        P ph[6][E];
-        line_fft<P, N, E, R, +1, 2, LY, truncated_slots(N, E, K)>(v, lds, l, t, twx);
-#pragma unroll
-        for (int s = 0; s < E; s++) { ph[0][s] = v[s].re; ph[1][s] = v[s].im; }
-        wait_vm<C::S>();                                       // fields 3-5
-        wave_fence();
-        gather(v, slot0 + 2 * RW, slot1);
-        lds_wait();                                            // slot0 read
-        request(slot0, more ? tile + 1 : tile, 0);
-        line_fft<P, N, E, R, +1, 2, LY, truncated_slots(N, E, K)>(v, lds, l, t, twx);
-#pragma unroll
-        for (int s = 0; s < E; s++) { ph[2][s] = v[s].re; ph[3][s] = v[s].im; }
-        gather(v, slot1 + RW, slot1 + 2 * RW);
-        lds_wait();                                            // slot1 read
-        request(slot1, more ? tile + 1 : tile, 3);
-        line_fft<P, N, E, R, +1, 2, LY, truncated_slots(N, E, K)>(v, lds, l, t, twx);
-#pragma unroll
-        for (int s = 0; s < E; s++) { ph[4][s] = v[s].re; ph[5][s] = v[s].im; }
-        // ph: 0 u_x, 1 u_y, 2 u_z, 3 omega_x, 4 omega_y, 5 omega_z
-        if (stage == 0) {
-#pragma unroll
-            for (int s = 0; s < E; s++) {
-                const P a = fabs(ph[0][s]) + fabs(ph[1][s]) + fabs(ph[2][s]);
-                umx = a > umx ? a : umx;
-            }
-        }
-        Cx<P> d1[E], d2[E];
-#pragma unroll
-        for (int s = 0; s < E; s++) {
-            d1[s] = {ph[1][s] * ph[5][s] - ph[2][s] * ph[4][s], ph[2][s] * ph[3][s] - ph[0][s] * ph[5][s]};
-            d2[s] = {ph[0][s] * ph[4][s] - ph[1][s] * ph[3][s], P(0)};
-        }
-        line_fft_T<P, N, E, R, -1, 2, LY>(d1, lds, l, t, twx);        // d1[m] = D1[t + M m]
-        line_fft_T<P, N, E, R, -1, 2, LY>(d2, lds, l, t, twx);
-        wave_fence();
-#pragma unroll
-        for (int m = 0; m < E; m++)          // the split reads only the partner positions 0 and >= N - K
-            if (m == 0 || M * m + M - 1 >= N - K) lds_put<P>(lds, LY::slot(t + M * m, l), d1[m]);
-        wave_fence();
-        // split D1 into the x-spectra of n_x and n_y
-        Cx<P> ox[E], oy[E];
-#pragma unroll
-        for (int m = 0; m < E; m++) {
-            const int k = t + M * m;
-            if (M * m <= K && (M * m + M - 1 <= K || k <= K)) {
-                const Cx<P> a = d1[m];
-                const Cx<P> b = lds_get<P>(lds, LY::slot((N - k) % N, l));
-                const P h = P(0.5);
-                ox[m] = {h * (a.re + b.re), h * (a.im - b.im)};
-                oy[m] = {h * (a.im + b.im), h * (b.re - a.re)};
-            }
-        }
-        wave_fence();
-#pragma unroll
-        for (int m = 0; m < E; m++) {
-            const int k = t + M * m;
-            if (M * m <= K && (M * m + M - 1 <= K || k <= K)) {
-                lds_put<P>(lds, l * (K + 1) + k, ox[m]);
-                lds_put<P>(lds, RWO + l * (K + 1) + k, oy[m]);
-                lds_put<P>(lds, 2 * RWO + l * (K + 1) + k, d2[m]);
-            }
-        }
-        wave_fence();
-        store_tile(tile, false);
-        if (more) {                                            // first pair of the next tile
-            wait_vm<C::D3 + C::S>();
-            wave_fence();
-            gather(v, slot0, slot0 + RW);
-        }
-    }
-    wait_vm<0>();                                              // no copy into LDS outlives the workgroup
-    if (stage == 0) {
+    gather(v, slot(0), slot(0) + RW);
+    // fold the member's max(|u|+|v|+|w|) over the wave and into its state
+    auto flush_max = [&](int m) {
         double dm = (double)umx;
 #pragma unroll
         for (int off = 32; off > 0; off >>= 1) {
             const double o = __shfl_xor(dm, off, 64);
             dm = o > dm ? o : dm;
         }
-        if (threadIdx.x == 0) atomicMax(&md.st->umax_bits, (unsigned long long)__double_as_longlong(dm));
-    }
-}
-
-// Wave-private x pass with the six input fields staged as three pairs through
-// two buffers of two fields each (instead of two buffers of three): pair q of
-// the wave's sequence (3 per tile) goes to buffer q mod 2 and is requested as
-// soon as pair q - 2 has been read from it, so two pairs are resident or in
-// flight at any time.  A third less staging LDS per wave than k_xpass_wave
-// (19.5 against 24.8 KB for 256-point FP32 rows), so that eight one-wave
-// workgroups share a compute unit, two per SIMD, where six leave two SIMDs
-// with a single wave.
-template <typename P, int N, int E_> struct XW2Cfg {
-    using B = XWCfg<P, N, E_>;
-    static constexpr int D2 = dma_tile_ops<2, B::RV, 64>();    // copies per pair
-    static constexpr long long LDS_BYTES = (4LL * B::RW + B::XL + B::NTW) * B::CS + 64;
-    static constexpr int WPS = (int)(163840 / ((LDS_BYTES + 511) / 512 * 512)) / 4;
-    static constexpr int MINW = WPS < 1 ? 1 : (WPS > 4 ? 4 : WPS);
-    static_assert(D2 + B::S < 64, "vector-memory count of the x-pass tile");
-};
-
-template <typename P, int N, int EV>
-__global__ void __launch_bounds__(64, (XW2Cfg<P, N, EV>::MINW)) k_xpass_wave2(const MemberDev *__restrict__ mems, const Cx<P> *__restrict__ tw, int stage) {
-    using C = XWCfg<P, N, EV>;
-    using C2 = XW2Cfg<P, N, EV>;
-    using LY = WaveLay<P, N>;
-    constexpr int E = C::E, M = C::M, R = C::R, K = C::K, RW = C::RW, RQ = C::RQ;
-    constexpr int RWO = C::RWO, RVO = C::RVO, D2 = C2::D2, S = C::S;
-    constexpr long long FSB = (long long)N * N * RQ * C::CS;         // bytes per input field
-    constexpr long long FSBO = (long long)N * N * (K + 1) * C::CS;   // bytes per output field
-    __shared__ __attribute__((aligned(16))) LdsT<P> slotA[2 * RW];
-    __shared__ __attribute__((aligned(16))) LdsT<P> slotB[2 * RW];
-    __shared__ __attribute__((aligned(16))) LdsT<P> lds[C::XL];
-    __shared__ Cx<P> twl[C::NTW];
-    unsigned chunk, mem_i;
-    xcd_tile(chunk, mem_i);
-    const MemberDev &md = mems[mem_i];
-    const int t0 = (int)((long long)chunk * C::TILES / gridDim.x);
-    const int t1 = (int)((long long)(chunk + 1) * C::TILES / gridDim.x);
-    if (t0 >= t1) return;                                     // uniform over the wave
-    const int t = (int)threadIdx.x % M, l = (int)threadIdx.x / M;
-    TwRegs<P, N, E> twr;
-    if constexpr (C::REGTW) twr.load(tw, t);
-    else for (int i = (int)threadIdx.x; i < C::NTW; i += 64) twl[i] = tw[i];
-    wave_fence();
-    const auto &twx = [&]() -> const auto & {
-        if constexpr (C::REGTW) return twr;
-        else return twl;
-    }();
-    const char *inb = (const char *)md.bufB;
-    char *outb = (char *)md.bufA;
-    auto slot = [&](int i) -> LdsT<P> * { return i ? slotB : slotA; };
-    auto request = [&](LdsT<P> *dst, int tile, int pair) {    // fields 2 pair, 2 pair + 1 of the tile's R rows
-        dma_tile<2, C::RV, 64>(dst, inb + (long long)(2 * pair) * FSB + (long long)tile * RW * C::CS, FSB);
+        if (threadIdx.x == 0) atomicMax(&mems[m].st->umax_bits, (unsigned long long)__double_as_longlong(dm));
+        umx = P(0);
     };
-    auto gather = [&](Cx<P> *v, const LdsT<P> *fa, const LdsT<P> *fb) {
-#pragma unroll
-        for (int m = 0; m < E; m++) {
-            const int n = t + M * m;
-            const int r = l * RQ;
-            if (M * m > K && M * m + M - 1 < N - K) {
-                v[m] = czero<P>();
-            } else if (m > 0 && M * m + M - 1 <= K) {
-                const Cx<P> A = lds_get<P>(fa, r + n), B = lds_get<P>(fb, r + n);
-                v[m] = {A.re - B.im, A.im + B.re};
-            } else if (M * m >= N - K) {
-                const Cx<P> A = lds_get<P>(fa, r + N - n), B = lds_get<P>(fb, r + N - n);
-                v[m] = {A.re + B.im, B.re - A.im};
-            } else {
-                const bool lo = n <= K, hi = n >= N - K;
-                const int kx = lo ? n : N - n;
-                Cx<P> A = czero<P>(), B = czero<P>();
-                if (lo || hi) { A = lds_get<P>(fa, r + kx); B = lds_get<P>(fb, r + kx); }
-                if (n == 0) v[m] = {A.re, B.re};
-                else if (lo) v[m] = {A.re - B.im, A.im + B.re};
-                else v[m] = {A.re + B.im, B.re - A.im};
-            }
-        }
-    };
-    P umx = P(0);
-    Cx<P> v[E];
-    typedef float F4 __attribute__((ext_vector_type(4)));
-    const unsigned lane16 = (threadIdx.x & 63u) * 16u;
-    auto store_tile = [&](int tile, bool zero) {
-        constexpr int NCF = (RVO + 63) / 64, NCH = 3 * NCF;
-#pragma unroll
-        for (int c = 0; c < NCH; c++) {
-            const int f = c / NCF, q = c - f * NCF;
-            const int st = q * 64 < RVO - 64 ? q * 64 : RVO - 64;
-            const F4 x = zero ? F4{0.f, 0.f, 0.f, 0.f} : *(const F4 *)((const char *)lds + (f * RVO + st) * 16 + lane16);
-            ENS_GLOBAL char *dst = (ENS_GLOBAL char *)outb + f * FSBO + (long long)tile * RWO * C::CS + st * 16;
-            *(ENS_GLOBAL F4 *)(dst + lane16) = x;
-        }
-    };
-    // Wait accounting (vector-memory operations complete in issue order).  The
-    // wave's pair requests R(q), q = 3 (tile - t0) + j, and its tile stores
-    // S(tile) are issued in the order ... R(3u+1) S(u-1) R(3u+2) R(3u+3) R(3u+4)
-    // S(u) ..., so before reading pair 0 of tile u at most D2 + S operations
-    // issued after it may be outstanding, before pair 1 S + D2, before pair 2
-    // D2.  The prologue writes zeros to the first tile's output to reproduce
-    // that order; requests past the last tile repeat the last tile's pairs.
-    request(slot(0), t0, 0);
-    request(slot(1), t0, 1);
-    store_tile(t0, true);
-    wait_vm<D2 + S>();                                         // pair 0 of the first tile
-    wave_fence();
-    gather(v, slot(0), slot(0) + RW);
-    for (int tile = t0; tile < t1; tile++) {
-        const int u = (tile - t0) & 1;                         // pairs 0, 1, 2 of this tile in slots u, 1 - u, u
-        const bool more = tile + 1 < t1;
-        const int nxt = more ? tile + 1 : tile;
+    for (int u = 0;; u = 1 - u) {                              // pairs 0, 1, 2 of this tile in slots u, 1 - u, u
+        const bool more = f - nw >= lo;
+        const At nxt = more ? at(f - nw) : cur;
         P ph[6][E];
         lds_wait();                                            // pair 0 read
-        request(slot(u), tile, 2);
+        request(slot(u), cur, 2);
         line_fft<P, N, E, R, +1, 2, LY, truncated_slots(N, E, K)>(v, lds, l, t, twx);
 #pragma unroll
         for (int s = 0; s < E; s++) { ph[0][s] = v[s].re; ph[1][s] = v[s].im; }
@@ -938,23 +776,18 @@ __global__ void __launch_bounds__(64, (XW2Cfg<P, N, EV>::MINW)) k_xpass_wave2(co
             }
         }
         wave_fence();
-        store_tile(tile, false);
+        store_tile(cur, false);
         if (more) {                                            // pair 0 of the next tile, in slot 1 - u
             wait_vm<D2 + S>();
             wave_fence();
             gather(v, slot(1 - u), slot(1 - u) + RW);
         }
+        if (stage == 0 && (!more || nxt.mem != cur.mem)) flush_max(cur.mem);
+        if (!more) break;
+        f -= nw;
+        cur = nxt;
     }
     wait_vm<0>();                                              // no copy into LDS outlives the workgroup
-    if (stage == 0) {
-        double dm = (double)umx;
-#pragma unroll
-        for (int off = 32; off > 0; off >>= 1) {
-            const double o = __shfl_xor(dm, off, 64);
-            dm = o > dm ? o : dm;
-        }
-        if (threadIdx.x == 0) atomicMax(&md.st->umax_bits, (unsigned long long)__double_as_longlong(dm));
-    }
 }
 
 // ================================================================== yfwd
@@ -1283,26 +1116,7 @@ static hipError_t run_xpass_dma(const MemberDev *mem, int count, int stage, cons
     return hipGetLastError();
 }
 
-// Wave-private x pass: one-wave workgroups, as many as stay resident,
-// split evenly over the members.
-template <typename P, int N, int EV>
-static hipError_t run_xpass_wave(const MemberDev *mem, int count, int stage, const Cx<P> *tw, hipStream_t s) {
-    using C = XWCfg<P, N, EV>;
-    static int resident = 0;
-    if (resident == 0) {
-        int dev = 0, cus = 0, occ = 0;
-        hipError_t e = hipGetDevice(&dev);
-        if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
-        if (e == hipSuccess) e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, k_xpass_wave<P, N, EV>, 64, 0);
-        if (e != hipSuccess) return e;
-        resident = (cus > 0 ? cus : 1) * (occ > 0 ? occ : 1);
-    }
-    int per = resident / (count > 0 ? count : 1);
-    per = per < 1 ? 1 : (per > C::TILES ? C::TILES : per);
-    k_xpass_wave<P, N, EV><<<dim3((unsigned)per, count), 64, 0, s>>>(mem, tw, stage);
-    return hipGetLastError();
-}
-
+// Wave-private x pass: one-wave workgroups, as many as stay resident.
 template <typename P, int N, int EV>
 static hipError_t run_xpass_wave2(const MemberDev *mem, int count, int stage, const Cx<P> *tw, hipStream_t s) {
     using C = XWCfg<P, N, EV>;
@@ -1315,9 +1129,10 @@ static hipError_t run_xpass_wave2(const MemberDev *mem, int count, int stage, co
         if (e != hipSuccess) return e;
         resident = (cus > 0 ? cus : 1) * (occ > 0 ? occ : 1);
     }
-    int per = resident / (count > 0 ? count : 1);
-    per = per < 1 ? 1 : (per > C::TILES ? C::TILES : per);
-    k_xpass_wave2<P, N, EV><<<dim3((unsigned)per, count), 64, 0, s>>>(mem, tw, stage);
+    const long long tiles = (long long)count * C::TILES;
+    const long long fit = resident < tiles ? resident : tiles;
+    const unsigned grid = (unsigned)(fit < 8 ? 8 : fit);       // a wave at least for every range
+    k_xpass_wave2<P, N, EV><<<dim3(grid), 64, 0, s>>>(mem, count, tw, stage);
     return hipGetLastError();
 }
 
@@ -1331,29 +1146,17 @@ static hipError_t run_pass(int pass, int variant, const MemberDev *mem, int coun
             if constexpr (N >= 64) return run_xpass_dma<P, N, 8>(mem, count, stage, twp, s);
             else return run_pencil<P, N, 8>(pass, mem, count, stage, twp, s);   // lines too short to stream
         }
-        if (pass == P_XPASS && variant == 6) {
-            // wave-private, pairs staged through two buffers: 16 (FP32) / 8 (FP64) values per thread
-            constexpr int EA = sizeof(P) == 4 ? 16 : 8, CS = (int)sizeof(Cx<P>);
-            if constexpr (N >= 64 && xwave_ok(N, EA, CS)) return run_xpass_wave2<P, N, EA>(mem, count, stage, twp, s);
-            else if constexpr (N >= 64) return run_xpass_dma<P, N, 8>(mem, count, stage, twp, s);
-            else return run_pencil<P, N, 8>(pass, mem, count, stage, twp, s);
-        }
         if (pass == P_XPASS && variant == 5) {
             // the plane pass where it exists; stage + 4: without the band step
             if constexpr (plane_ok(N))
                 return launch_plane(N, sizeof(P) == 4 ? ENS_FP32 : ENS_FP64, mem, count, stage & 3, stage < 4, tw, s);
         }
-        if (pass == P_XPASS && (variant == 4 || variant == 5)) {
-            // wave-private: 16 (FP32) / 8 (FP64) values per thread, or half that
-            // (where that tile shape is invalid: the streamed x pass, variant 2)
-            constexpr int EA = sizeof(P) == 4 ? 16 : 8, EB = EA / 2, CS = (int)sizeof(Cx<P>);
-            if constexpr (N >= 64) {
-                if constexpr (xwave_ok(N, EA, CS))
-                    if (variant == 4) return run_xpass_wave<P, N, EA>(mem, count, stage, twp, s);
-                if constexpr (xwave_ok(N, EB, CS) && !plane_ok(N))
-                    if (variant == 5) return run_xpass_wave<P, N, EB>(mem, count, stage, twp, s);
-                return run_xpass_dma<P, N, 8>(mem, count, stage, twp, s);
-            } else return run_pencil<P, N, 8>(pass, mem, count, stage, twp, s);
+        if (pass == P_XPASS && variant >= 4) {
+            // wave-private, pairs staged through two buffers: 16 (FP32) / 8 (FP64) values per thread
+            constexpr int EA = sizeof(P) == 4 ? 16 : 8, CS = (int)sizeof(Cx<P>);
+            if constexpr (N >= 64 && xwave_ok(N, EA, CS)) return run_xpass_wave2<P, N, EA>(mem, count, stage, twp, s);
+            else if constexpr (N >= 64) return run_xpass_dma<P, N, 8>(mem, count, stage, twp, s);
+            else return run_pencil<P, N, 8>(pass, mem, count, stage, twp, s);
         }
         if (pass == P_XPASS && variant == 3) {
             // streamed, 16 values per thread (one LDS exchange per 256-point
@@ -1414,6 +1217,12 @@ hipError_t launch_pass(int pass, int variant, int n, int prec, const MemberDev *
                             : dispatch_n<double>(n, pass, variant, mem, count, stage, tw, s);
 }
 
+// Variants of the x pass that are another one's kernel: 4, and 5 where there
+// is no plane pass, are 6.
+bool variant_distinct(int pass, int n, int variant) {
+    return pass != P_XPASS || (variant != 4 && (variant != 5 || plane_ok(n)));
+}
+
 int pass_variants(int pass) {
     if (pass == P_XPASS) return 7;
     if (pass == P_ZFWD) return 2;                               // 1: fused with the next stage's z inverse
@@ -1422,8 +1231,17 @@ int pass_variants(int pass) {
 }
 
 int default_variant(int pass, int n, int prec) {
-    if (pass == P_XPASS) return plane_ok(n) ? 5 : 2;           // plane pass; streamed, 8 values per thread
-    if (pass == P_ZINV || pass == P_YINV || pass == P_YFWD) return prec == ENS_FP32 ? 1 : 0;
+    // x pass: the plane pass where it exists; the wave-private pass from n = 256
+    // (one member, us a step: 256 FP32 307 against 311 and more, 256 FP64 582 /
+    // 676, 512 FP32 2248 / 2879) and at 128 in FP64 (four members 295 / 340); at
+    // 128 in FP32 the streamed pass with 16 values per thread (six members 222 /
+    // 232); at 1024 the streamed one with 8 (the wave-private one spills)
+    if (pass == P_XPASS)
+        return plane_ok(n) ? 5 : n == 1024 ? 2 : (n == 128 && prec == ENS_FP32) ? 3 : 6;
+    // y and z passes: 8 values per thread; 16 in FP32 only for the y inverse at
+    // n = 256 (287 against 303 us a step) and, not measured again, at n = 1024
+    if (pass == P_YINV) return prec == ENS_FP32 && n >= 256 && n != 512 ? 1 : 0;
+    if (pass == P_ZINV || pass == P_YFWD) return prec == ENS_FP32 && n == 1024 ? 1 : 0;
     // fused z forward: 0.4-1.8 % faster per step up to n = 512 (both
     // precisions); at n = 1024 its registers spill and it gains nothing
     if (pass == P_ZFWD) return n <= 512 ? 1 : 0;

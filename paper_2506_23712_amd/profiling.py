@@ -84,10 +84,8 @@ def kernel_name(pass_name: str, n: int, prec: str, variant) -> str:
     ea = 16 if prec == "fp32" else 8
     if pass_name == "xpass" and variant == 5 and n <= 64:       # the plane pass (y inverse, x pass, y forward)
         return f"ens::k_plane<{p}, {n}>"
-    if pass_name == "xpass" and variant == 6 and n >= 64:
+    if pass_name == "xpass" and variant in (4, 5, 6) and n >= 64:
         return f"ens::k_xpass_wave2<{p}, {n}, {ea}>"
-    if pass_name == "xpass" and variant in (4, 5) and n >= 64:
-        return f"ens::k_xpass_wave<{p}, {n}, {ea if variant == 4 else ea // 2}>"
     if pass_name == "xpass" and variant == 3 and 128 <= n <= 512 and prec == "fp32":
         return f"ens::k_xpass_dma<{p}, {n}, 16>"
     if pass_name == "xpass" and variant in (2, 3) and n >= 64:
