@@ -73,17 +73,22 @@ template <typename P, int N, int E_, int TM = 1> struct Cfg {
     // as the z inverse's output) instead of in blocks of z: where the plane pass
     // writes them (it owns a plane, so a plane's values are contiguous)
     static constexpr bool PLN = plane_ok(N);
-    // z forward + update: 8 values per thread, 512 threads up to N = 256;
-    // 16 values per thread and the pencil rule above for longer lines; 128
-    // threads for N <= 64, whose members have few lines (15 workgroups of 512
-    // threads for a 64^3 member, 2 for a 32^3 one, on 256 compute units)
-    static constexpr int EZ = N <= 256 ? 8 : 16, MZ = N / EZ;
-    static constexpr int TZ = N <= 64 ? (N == 16 ? 32 : 128 / MZ) : N <= 256 ? 512 / MZ : (TL * MZ <= 512 ? TL : 512 / MZ);
+    // z forward + update: 8 values per thread (16 at N = 1024) and, from N =
+    // 128, one 128-byte line per position, the smallest workgroup that stores
+    // whole lines: its phases (loads, transforms, update, transforms) are apart
+    // by barriers, and several small workgroups on a compute unit overlap them
+    // where one of 512 threads per compute unit (FP64) had nothing beside it.
+    // us a step against 512 threads: eight 128^3 FP64 members 521 -> 468, one
+    // 256^3 FP64 member 525 -> 484, six 128^3 FP32 members 196 -> 191; N = 512
+    // with 8 values (16: 212 registers FP32, one wave per SIMD in FP64): 2370 ->
+    // 2238 FP32, 4730 -> 4350 FP64.  128 threads for N <= 64, whose members
+    // have few lines (15 workgroups of 512 threads for a 64^3 member, 2 for a
+    // 32^3 one, on 256 compute units).
+    static constexpr int EZ = N <= 512 ? 8 : 16, MZ = N / EZ;
+    static constexpr int TZ = N <= 64 ? (N == 16 ? 32 : 128 / MZ) : N <= 512 ? TL : 512 / MZ;
     static constexpr int NTZ = TZ * MZ;
-    // z forward + update, waves per SIMD the register budget is cut for: two
-    // 512-thread workgroups per compute unit (4 waves per SIMD) in FP32; the
-    // FP64 update keeps its registers
-    static constexpr int ZMINB = (sizeof(P) == 4 && NTZ == 512 && EZ == 8) ? 4 : 1;
+    // z forward + update, waves per SIMD the register budget is cut for
+    static constexpr int ZMINB = N <= 64 || N == 1024 ? 1 : sizeof(P) == 4 ? 4 : 2;
 };
 
 // -------------------------------------------------------------------- band
