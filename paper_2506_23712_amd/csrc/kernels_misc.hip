@@ -267,24 +267,30 @@ hipError_t launch_fill_f64(double *p, long long n, double v, hipStream_t s) {
 
 // ------------------------------------------------------- batched pencil FFT
 // element j of line l at j * lines + l.  Bound by HBM: one read and one write
-// of the array, so what counts is that a workgroup's consecutive lines are
-// whole 128-byte runs at every position: T is at least 16 (FP32) / 8 (FP64)
-// lines, i.e. up to 1024 threads and 128 KiB of LDS at n = 1024.  With 256
-// threads whatever n, n = 512 FP32 moved runs of 64 bytes and n = 1024 of 32
-// bytes: 302 us for 87041 lines of n = 512 FP32, now 166 us (4.3 TB/s).
-// Neighbouring tiles run on one XCD (xcd_tile): where `lines` is no
-// multiple of T a run straddles a line that its neighbour reads or writes the
-// rest of.  Twiddles from LDS, as in the time-step passes.
-template <typename P, int N> struct PencilCfg {
-    static constexpr int E = 16, M = N / E, TL = 128 / (int)sizeof(Cx<P>);
-    static constexpr int T = 256 / M > TL ? 256 / M : TL, NT = T * M;
+// of the array, so what counts is the run of consecutive lines a workgroup
+// moves at every position, and a second workgroup on the compute unit that
+// loads while the first transforms.  From n = 256 a workgroup holds 64 KiB of
+// lines: runs of 256 bytes at n = 256, 128 at 512, 64 at 1024 (where whole
+// 128-byte runs, 128 KiB, were slower).  With 256 threads whatever n, n = 512
+// FP32 moved runs of 64 bytes and n = 1024 of 32 bytes: 302 us for 87041 lines
+// of n = 512 FP32, now 155 (4.6 TB/s).  Neighbouring tiles run on one XCD
+// (xcd_tile): where `lines` is no multiple of T a run straddles a line that its
+// neighbour reads or writes the rest of.  Twiddles from LDS, as in the time-step
+// passes.
+// Values per thread: 16, but 8 from n = 512 where the lines fill the chip (256
+// workgroups): more waves per compute unit (n = 512 FP32 174 -> 163 us, FP64 163
+// -> 153, n = 1024 FP32 191 -> 160, FP64 189 -> 169, in a loop of calls); with
+// few lines the smaller workgroups start sooner.
+template <typename P, int N, int E_> struct PencilCfg {
+    static constexpr int E = E_, M = N / E;
+    static constexpr int T = N >= 256 ? 65536 / (N * (int)sizeof(Cx<P>)) : 256 / M, NT = T * M;
     static_assert(NT <= 1024, "pencil workgroup");
 };
 
-template <typename P, int N, int DIR>
-__global__ void __launch_bounds__((PencilCfg<P, N>::NT)) k_fft_pencils(long long lines, const L2<P> *__restrict__ in, L2<P> *out,
+template <typename P, int N, int EV, int DIR>
+__global__ void __launch_bounds__((PencilCfg<P, N, EV>::NT)) k_fft_pencils(long long lines, const L2<P> *__restrict__ in, L2<P> *out,
                                                      const Cx<P> *__restrict__ twg) {
-    using C = PencilCfg<P, N>;
+    using C = PencilCfg<P, N, EV>;
     constexpr int E = C::E, M = C::M, T = C::T;
     __shared__ L2<P> lds[N * T];
     __shared__ Cx<P> tw[twiddle_span(N, E)];
@@ -310,16 +316,24 @@ __global__ void __launch_bounds__((PencilCfg<P, N>::NT)) k_fft_pencils(long long
     }
 }
 
-template <typename P, int N>
-static hipError_t pencils_n(int sign, long long lines, const void *in, void *out, const void *tw, hipStream_t s) {
-    constexpr int T = PencilCfg<P, N>::T, NT = PencilCfg<P, N>::NT;
-    const unsigned nb = (unsigned)((lines + T - 1) / T);
+template <typename P, int N, int EV>
+static hipError_t pencils_e(int sign, long long lines, const void *in, void *out, const void *tw, hipStream_t s) {
+    using C = PencilCfg<P, N, EV>;
+    const unsigned nb = (unsigned)((lines + C::T - 1) / C::T);
     const L2<P> *ip = reinterpret_cast<const L2<P> *>(in);
     L2<P> *op = reinterpret_cast<L2<P> *>(out);
     const Cx<P> *twp = reinterpret_cast<const Cx<P> *>(tw);
-    if (sign < 0) k_fft_pencils<P, N, -1><<<nb, NT, 0, s>>>(lines, ip, op, twp);
-    else k_fft_pencils<P, N, +1><<<nb, NT, 0, s>>>(lines, ip, op, twp);
+    if (sign < 0) k_fft_pencils<P, N, EV, -1><<<nb, C::NT, 0, s>>>(lines, ip, op, twp);
+    else k_fft_pencils<P, N, EV, +1><<<nb, C::NT, 0, s>>>(lines, ip, op, twp);
     return hipGetLastError();
+}
+
+template <typename P, int N>
+static hipError_t pencils_n(int sign, long long lines, const void *in, void *out, const void *tw, hipStream_t s) {
+    if constexpr (N >= 512) {
+        if (lines >= 256 * PencilCfg<P, N, 8>::T) return pencils_e<P, N, 8>(sign, lines, in, out, tw, s);
+    }
+    return pencils_e<P, N, 16>(sign, lines, in, out, tw, s);
 }
 
 template <typename P>

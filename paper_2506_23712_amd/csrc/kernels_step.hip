@@ -874,31 +874,7 @@ __global__ void __launch_bounds__((Cfg<P, N, 8>::NTZ), (Cfg<P, N, 8>::ZMINB)) k_
     const int kx = valid ? L % (K + 1) : 0;
     const uint32_t Lz = (uint32_t)iy * BL + (uint32_t)kx;      // position 0 of the line in bufB
     const int my = iy <= K ? iy : iy - (2 * K + 1);
-    // time step of this RK step
-    double dt;
-    if (md.dt_fixed > 0.0) dt = md.dt_fixed;
-    else if (stage == 0) {
-        const double um = __longlong_as_double((long long)md.st->umax_bits);
-        dt = um > 0.0 ? md.cfl * (md.box / N) / um : 0.0;
-    } else dt = md.st->dt;
-    if (stage == 0 && tile == 0 && threadIdx.x == 0) {
-        md.st->dt = dt;
-        if (!(dt > 0.0)) md.st->diag.flags |= 4;
-    }
-    const double Ef = md.st->Ef;
-    const P ffac = (P)(Ef > 0.0 ? md.eps_m / (2.0 * Ef) : 0.0);
-    const double RKA[3] = {0.0, -5.0 / 9.0, -153.0 / 128.0};
-    const double RKB[3] = {1.0 / 3.0, 15.0 / 16.0, 8.0 / 15.0};
-    const double RKH[3] = {1.0 / 3.0, 5.0 / 12.0, 1.0 / 4.0};
-    const P As = (P)RKA[stage], Bs = (P)RKB[stage], Pdt = (P)dt;
-    const double nh = md.nu * RKH[stage] * dt * md.dk * md.dk;   // exponent per |m|^2
-    // integrating factor exp(-nh |m|^2) = exp(-nh (m_x^2 + m_y^2)) exp(-nh m_z^2):
-    // one exponential per line and a table of the m_z factors per workgroup
-    for (int i = (int)threadIdx.x; i < N; i += NT) {
-        const double mz = (double)mode_of(i, N);
-        ezt[i] = exp(-nh * mz * mz);
-    }
-    const double exy = exp(-nh * (double)(kx * kx + my * my));
+    // every load first: the scalars and exponentials below hide part of their latency
     Cx<P> a[3][E];
 #pragma unroll
     for (int f = 0; f < 3; f++) {
@@ -936,6 +912,31 @@ __global__ void __launch_bounds__((Cfg<P, N, 8>::NTZ), (Cfg<P, N, 8>::ZMINB)) k_
         }
     };
     if constexpr (PRE) load_state(0);
+    // time step of this RK step
+    double dt;
+    if (md.dt_fixed > 0.0) dt = md.dt_fixed;
+    else if (stage == 0) {
+        const double um = __longlong_as_double((long long)md.st->umax_bits);
+        dt = um > 0.0 ? md.cfl * (md.box / N) / um : 0.0;
+    } else dt = md.st->dt;
+    if (stage == 0 && tile == 0 && threadIdx.x == 0) {
+        md.st->dt = dt;
+        if (!(dt > 0.0)) md.st->diag.flags |= 4;
+    }
+    const double Ef = md.st->Ef;
+    const P ffac = (P)(Ef > 0.0 ? md.eps_m / (2.0 * Ef) : 0.0);
+    const double RKA[3] = {0.0, -5.0 / 9.0, -153.0 / 128.0};
+    const double RKB[3] = {1.0 / 3.0, 15.0 / 16.0, 8.0 / 15.0};
+    const double RKH[3] = {1.0 / 3.0, 5.0 / 12.0, 1.0 / 4.0};
+    const P As = (P)RKA[stage], Bs = (P)RKB[stage], Pdt = (P)dt;
+    const double nh = md.nu * RKH[stage] * dt * md.dk * md.dk;   // exponent per |m|^2
+    // integrating factor exp(-nh |m|^2) = exp(-nh (m_x^2 + m_y^2)) exp(-nh m_z^2):
+    // one exponential per line and a table of the m_z factors per workgroup
+    for (int i = (int)threadIdx.x; i < N; i += NT) {
+        const double mz = (double)mode_of(i, N);
+        ezt[i] = exp(-nh * mz * mz);
+    }
+    const double exy = exp(-nh * (double)(kx * kx + my * my));
 #pragma unroll
     for (int f = 0; f < 3; f++) line_fft<P, N, E, T, -1>(a[f], lds, l, t, tw);
     __syncthreads();

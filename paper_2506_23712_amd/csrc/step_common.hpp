@@ -52,7 +52,8 @@ template <typename P, int N, int E_, int TM = 1> struct Cfg {
     }
     static constexpr int E = E_ > N ? N : E_;
     static constexpr int M = N / E;
-    // Lines per workgroup of the y/z pencil passes: at least 256 threads and
+    // Lines per workgroup of the y/z pencil passes: at least 256 threads (128 for
+    // N <= 64, whose members have few lines) and
     // at least one 128-byte line per position (16 FP32 / 8 FP64 consecutive
     // lines, a multiple of which is where every tile starts), so that every
     // store covers whole lines; at most 1024 threads (512
@@ -63,7 +64,7 @@ template <typename P, int N, int E_, int TM = 1> struct Cfg {
     // TM > 1 (autotuner variants 2, 3 of the y/z passes): TM times as many
     // lines, i.e. TM whole lines per position, where the thread budget above
     // allows it (not for 16 FP64 values per thread, which would spill)
-    static constexpr int T1 = N <= 256 ? (256 / M > TL ? 256 / M : TL) : (TL * M <= MAXT ? TL : MAXT / M);
+    static constexpr int T1 = N <= 64 ? (128 / M > TL ? 128 / M : TL) : N <= 256 ? (256 / M > TL ? 256 / M : TL) : (TL * M <= MAXT ? TL : MAXT / M);
     static constexpr int T = (T1 * TM * M <= MAXT && !(sizeof(P) == 8 && E >= 16)) ? T1 * TM : T1;
     static constexpr int NT = T * M;
     // z/y inverse passes: waves per SIMD the register budget is cut for

@@ -18,9 +18,10 @@ HK = dict(qr_bins=64, q_lo=-30.0, q_hi=30.0, r_lo=-60.0, r_hi=60.0, log_bins=128
 def test_pencils_around_a_workgroups_lines(n, prec):
     import torch
     import paper_2506_23712_amd as ens
-    T = max(256 // (n // 16), 16 if prec == "fp32" else 8)      # lines of a workgroup
+    T = 65536 // (n * (8 if prec == "fp32" else 16)) if n >= 256 else 256 // (n // 16)      # lines of a workgroup
     dt = torch.complex64 if prec == "fp32" else torch.complex128
-    for lines in (T - 1, T, T + 1, 8 * T + 3):
+    full = [256 * T - 1, 256 * T + 1] if n >= 512 else []        # where 8 values per thread take over
+    for lines in (T - 1, T, T + 1, 8 * T + 3, *full):
         rng = np.random.default_rng(n + lines)
         x = torch.from_numpy(rng.standard_normal((n, lines)) + 1j * rng.standard_normal((n, lines))).to(dt)
         ref = np.fft.fft(x.numpy().astype(np.complex128), axis=0)
