@@ -18,7 +18,7 @@ namespace ens {
 // members 196 -> 118 us, nine 64^3 FP64 members 278 -> 256 us.
 //
 // The plane lives in LDS as rows (f, kx) of N y positions.  Phase 1, one row per
-// group of M = N/8 (N = 16: 4) lanes: the row's spectral line (the vorticity's formed on
+// group of M = N/8 or N/4 lanes: the row's spectral line (the vorticity's formed on
 // load), inverse transform inside the row.  Phase 2, one y per group: the 3
 // pairs of fields inverse transformed along x, n = u x omega, forward, the
 // exchanges in the group's own column of the plane (the fields it has read).
@@ -31,14 +31,16 @@ namespace ens {
 // The workgroup after the last plane performs the member's band step, which
 // needs only the velocity, and which only the z forward waits for.
 template <typename P, int N> struct PlaneCfg {
-    static constexpr int K = N / 3, KX = K + 1, E = N == 16 ? 4 : 8, M = N / E;
+    static constexpr int K = N / 3, KX = K + 1, E = N == 16 || (N == 32 && sizeof(P) == 4) ? 4 : 8, M = N / E;
     static constexpr int ROWS = 6 * KX, NP = (2 * K + 1) * KX;
     static constexpr int PITCH = sizeof(P) == 4 ? N + 8 : N;
     // N = 64: 64 groups of 8 lanes take the 132, 64 and 66 lines of the phases
     // in 2, 1 and 1 rounds and a rest that one wave takes (8 waves, so that FP32
     // has two workgroups on a compute unit at 128 registers and FP64 256 registers);
-    // N = 32: 80 groups of 4 (66, 32, 33), N = 16: 48 of 4 (36, 16, 18)
-    static constexpr int NT = N == 64 ? 512 : N == 32 ? 320 : 192, G = NT / M;
+    // N = 32: 72 groups of 8 in FP32 (4 values per thread: 109 -> 104 us a step
+    // for 50 members; FP64 has no gain) or 80 of 4 (66, 32, 33 lines), N = 16: 48
+    // of 4 (36, 16, 18)
+    static constexpr int NT = N == 64 ? 512 : N == 32 ? (E == 4 ? 576 : 320) : 192, G = NT / M;
     static constexpr int MINW = N == 64 ? (sizeof(P) == 4 ? 4 : 2) : 1;   // waves per SIMD
     static constexpr int RPW = 64 / M;                         // columns of a wave in phase 2
     // FP64: each thread's twiddles in registers (a table in LDS is read at

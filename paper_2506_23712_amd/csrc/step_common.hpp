@@ -74,19 +74,22 @@ template <typename P, int N, int E_, int TM = 1> struct Cfg {
     // as the z inverse's output) instead of in blocks of z: where the plane pass
     // writes them (it owns a plane, so a plane's values are contiguous)
     static constexpr bool PLN = plane_ok(N);
-    // z forward + update: 8 values per thread (16 at N = 1024) and, from N =
-    // 128, one 128-byte line per position, the smallest workgroup that stores
-    // whole lines: its phases (loads, transforms, update, transforms) are apart
-    // by barriers, and several small workgroups on a compute unit overlap them
-    // where one of 512 threads per compute unit (FP64) had nothing beside it.
-    // us a step against 512 threads: eight 128^3 FP64 members 521 -> 468, one
-    // 256^3 FP64 member 525 -> 484, six 128^3 FP32 members 196 -> 191; N = 512
-    // with 8 values (16: 212 registers FP32, one wave per SIMD in FP64): 2370 ->
-    // 2238 FP32, 4730 -> 4350 FP64.  128 threads for N <= 64, whose members
-    // have few lines (15 workgroups of 512 threads for a 64^3 member, 2 for a
-    // 32^3 one, on 256 compute units).
-    static constexpr int EZ = N <= 512 ? 8 : 16, MZ = N / EZ;
-    static constexpr int TZ = N <= 64 ? (N == 16 ? 32 : 128 / MZ) : N <= 512 ? TL : 512 / MZ;
+    // z forward + update: one 128-byte line per position from N = 128, the
+    // smallest workgroup that stores whole lines: its phases (loads, transforms,
+    // update, transforms) are apart by barriers, and several small workgroups on
+    // a compute unit overlap them where one of 512 threads per compute unit
+    // (FP64) had nothing beside it.  us a step against 512 threads: eight 128^3
+    // FP64 members 521 -> 468, one 256^3 FP64 member 525 -> 484, six 128^3 FP32
+    // members 196 -> 191; N = 512 with 8 values (16: 212 registers FP32, one wave
+    // per SIMD in FP64): 2370 -> 2238 FP32, 4730 -> 4350 FP64.  At least 128
+    // threads for N <= 64, whose members have few lines (15 workgroups of 512
+    // threads for a 64^3 member, 2 for a 32^3 one, on 256 compute units).
+    // Values per thread: 8; 4 for N <= 64, where a wave's own instructions are
+    // the time (us a step, one 32^3 FP64 member 37 -> 29, nine 64^3 FP64 members
+    // 88 -> 76, 47 of 64^3 FP32 equal), and in FP64 at N = 128 (eight members 468
+    // -> 454; FP32 191 -> 199; FP64 at N = 256 484 -> 567); 16 at N = 1024.
+    static constexpr int EZ = N <= 64 || (sizeof(P) == 8 && N == 128) ? 4 : N <= 512 ? 8 : 16, MZ = N / EZ;
+    static constexpr int TZ = N <= 64 ? (128 / MZ > TL ? 128 / MZ : TL) : N <= 512 ? TL : 512 / MZ;
     static constexpr int NTZ = TZ * MZ;
     // z forward + update, waves per SIMD the register budget is cut for
     static constexpr int ZMINB = N <= 64 || N == 1024 ? 1 : sizeof(P) == 4 ? 4 : 2;
