@@ -183,8 +183,9 @@ ens_status ens_step(ens_ctx *ctx, const int32_t *members, int32_t count, int32_t
  * 2 y inverse, 3 x fused (c2r, u x omega, r2c), 4 y forward,
  * 5 z forward + projection + forcing + update, 6 end-of-step reduction.
  * With the fused z forward (pass 5 variant 1) the z inverse of stages 2 and
- * 3 runs inside pass 5 and is counted there; with the plane pass (pass 3
- * variant 5, n <= 64) passes 0, 2 and 4 run inside pass 3. */
+ * 3 runs inside pass 5 and is counted there; the band energy runs beside the
+ * y inverse (ms_out[0] is 0); with the plane pass (pass 3 variant 5, n <= 64)
+ * passes 0, 2 and 4 run inside pass 3. */
 #define ENS_NPASS 7
 ens_status ens_profile_step(ens_ctx *ctx, const int32_t *members, int32_t count, void *stream,
                             double *ms_out);

@@ -291,11 +291,12 @@ bool zinv_fused(const ens_ctx *ctx, int pass, int stage, int n, int prec, StepKi
     return pass == P_ZINV && variant_of(ctx, P_ZFWD, n, prec) == 1 && (stage > 0 || k.zinv0_done);
 }
 
-// Passes another launch of the stage performs: the fused z inverse, and with
-// the plane pass (an x-pass variant) the band step and the y passes.
+// Passes another launch of the stage performs: the band step (the y inverse or
+// the plane pass does it), the fused z inverse, and with the plane pass (an
+// x-pass variant) the y passes.
 bool pass_done(const ens_ctx *ctx, int pass, int stage, int n, int prec, StepKind k) {
-    if ((pass == P_BAND || pass == P_YINV || pass == P_YFWD) && plane_pass(n, variant_of(ctx, P_XPASS, n, prec)))
-        return true;
+    if (pass == P_BAND) return true;
+    if ((pass == P_YINV || pass == P_YFWD) && plane_pass(n, variant_of(ctx, P_XPASS, n, prec))) return true;
     return zinv_fused(ctx, pass, stage, n, prec, k);
 }
 
@@ -1044,8 +1045,8 @@ ENS_API ens_status ens_autotune(ens_ctx *ctx, const int32_t *members, int32_t co
                 auto go = [&](int p, int var, int stage) { return launch_pass(p, var, g.n, g.prec, g.dev, cnt, stage, g.tw, s); };
                 if (xp && plane_pass(g.n, v)) return go(pass, v, 1 + 4);
                 if (xp)
-                    if (hipError_t e = go(P_YINV, variant_of(ctx, P_YINV, g.n, g.prec), 1)) return e;
-                if (hipError_t e = go(pass, v, 1)) return e;
+                    if (hipError_t e = go(P_YINV, variant_of(ctx, P_YINV, g.n, g.prec), 1 + 4)) return e;
+                if (hipError_t e = go(pass, v, pass == P_YINV ? 1 + 4 : 1)) return e;
                 if (!plane) return hipSuccess;
                 return go(P_YFWD, variant_of(ctx, P_YFWD, g.n, g.prec), 1);
             };

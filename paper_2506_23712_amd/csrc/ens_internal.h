@@ -137,8 +137,8 @@ hipError_t launch_pass(int pass, int variant, int n, int prec, const MemberDev *
 int pass_variants(int pass);
 bool variant_distinct(int pass, int n, int variant);   // false: the kernel of another variant (not timed)
 // Whether x-pass variant `variant` at grid size n is the plane pass, which also
-// performs the y inverse, the y forward and (at stage < 4; not at stage + 4)
-// the band step.
+// performs the y inverse and the y forward.  The plane pass and the y inverse
+// perform the band step at stage < 4 and leave it out at stage + 4.
 bool plane_pass(int n, int variant);
 hipError_t launch_plane(int n, int prec, const MemberDev *mem, int count, int stage, bool band, const void *tw, hipStream_t s);
 int default_variant(int pass, int n, int prec);

@@ -2,8 +2,8 @@
 // side and update, for a batch of members of one grid size and precision.
 //
 // Data flow of a stage (K = N/3, retained set |m_i| <= K, half space m_x >= 0):
-//   band   : E_f = (1/2) sum_band |u_hat|^2 (FP64)                (tiny kernel)
 //   zinv   : u_hat_c -> Z^-1[u_hat_c], Z^-1[i k_z u_hat_c]         5 fields
+//   band   : E_f = (1/2) sum_band |u_hat|^2 (FP64), one workgroup of the yinv launch
 //   yinv   : -> u_x,u_y,u_z, omega_x,omega_y,omega_z  (y physical)   6 fields
 //   xpass  : c2r along x, n = u x omega, r2c along x, keep m_x <= K  3 fields
 //   yfwd   : forward along y, keep |m_y| <= K                         3 fields
@@ -24,13 +24,6 @@
 #include "step_common.hpp"
 
 namespace ens {
-
-// ================================================================== band
-template <typename P>
-__global__ void __launch_bounds__(256) k_band_energy(const MemberDev *__restrict__ mems, int stage) {
-    __shared__ double red[256];
-    band_energy<P, 256>(mems[blockIdx.x], stage, red);
-}
 
 // Loads of one pencil (E values of line L at positions t + M m), truncated:
 // position p holds mode m = p or p - N; only |m| <= K is stored, at index
@@ -102,16 +95,29 @@ __global__ void __launch_bounds__((Cfg<P, N, EV, TM>::NT), (Cfg<P, N, EV, TM>::P
 // y-lines L = z (K+1) + kx.  in bufA [5][N (z)][ZP] (line L at iy (K+1) of
 // plane z); out bufB [6][N / ZB][N (y)][BL] (Cfg::yel):
 // u_x, u_y, u_z, omega_x, omega_y, omega_z
+// The first workgroup of a member (stage >= 0) performs its band step, which
+// needs only the velocity and which only the z forward waits for: as a launch
+// of its own it added 6 us to every stage (6 % of the step of one 128^3 member).
+// The z inverse has by then read the velocity before the band's part of the
+// m_x = 0 plane is made Hermitian; what that removes is the part of the plane
+// whose transform is imaginary, and the x pass takes the real part at m_x = 0.
 template <typename P, int N, int EV, int TM = 1>
-__global__ void __launch_bounds__((Cfg<P, N, EV, TM>::NT)) k_yinv(const MemberDev *__restrict__ mems, const Cx<P> *__restrict__ twg) {
+__global__ void __launch_bounds__((Cfg<P, N, EV, TM>::NT)) k_yinv(const MemberDev *__restrict__ mems, const Cx<P> *__restrict__ twg, int stage) {
     using C = Cfg<P, N, EV, TM>;
     constexpr int E = C::E, M = C::M, T = C::T, KX = C::KX, ZP = C::ZP, NYL = C::NYL;
     __shared__ LdsT<P> lds[N * T];
     __shared__ Cx<P> tw[twiddle_span(N, E)];               // twiddles in LDS: no global load inside the transforms
-    for (int i = (int)threadIdx.x; i < twiddle_span(N, E); i += (int)blockDim.x) tw[i] = twg[i];
     unsigned tile, mem_i;
     xcd_tile(tile, mem_i);
     const MemberDev &md = mems[mem_i];
+    if (stage >= 0) {
+        if (tile == 0) {                                       // uniform over the workgroup
+            band_energy<P, (C::NT >= 256 ? 256 : 128)>(md, stage, reinterpret_cast<double *>(lds));
+            return;
+        }
+        tile--;
+    }
+    for (int i = (int)threadIdx.x; i < twiddle_span(N, E); i += (int)blockDim.x) tw[i] = twg[i];
     const int l = threadIdx.x % T, t = threadIdx.x / T;
     const int L = tile * T + l;
     const bool inb = L < NYL;
@@ -1089,7 +1095,10 @@ static hipError_t run_pencil(int pass, const MemberDev *mem, int count, int stag
     using C = Cfg<P, N, EV, TM>;
     switch (pass) {
     case P_ZINV: k_zinv<P, N, EV, TM><<<dim3((C::ZP + C::T - 1) / C::T, count), C::NT, 0, s>>>(mem, tw); break;
-    case P_YINV: k_yinv<P, N, EV, TM><<<dim3((C::NYL + C::T - 1) / C::T, count), C::NT, 0, s>>>(mem, tw); break;
+    case P_YINV:                                               // stage + 4: without the band step
+        static_assert(C::NT >= 128 && N * C::T * (int)sizeof(Cx<P>) >= 2048, "band step in the y inverse's workgroup");
+        k_yinv<P, N, EV, TM><<<dim3((C::NYL + C::T - 1) / C::T + (stage < 4 ? 1 : 0), count), C::NT, 0, s>>>(mem, tw, stage < 4 ? stage : -1);
+        break;
     case P_XPASS: k_xpass<P, N, EV><<<dim3((unsigned)((long long)N * N / C::TX), count), 256, 0, s>>>(mem, tw, stage); break;
     case P_YFWD: k_yfwd<P, N, EV, TM><<<dim3((C::NYL + C::T - 1) / C::T, count), C::NT, 0, s>>>(mem, tw); break;
     default: return hipErrorInvalidValue;
@@ -1209,11 +1218,6 @@ static hipError_t dispatch_n(int n, int pass, int variant, const MemberDev *mem,
 
 hipError_t launch_pass(int pass, int variant, int n, int prec, const MemberDev *mem, int count, int stage,
                        const void *tw, hipStream_t s) {
-    if (pass == P_BAND) {
-        if (prec == ENS_FP32) k_band_energy<float><<<count, 256, 0, s>>>(mem, stage);
-        else k_band_energy<double><<<count, 256, 0, s>>>(mem, stage);
-        return hipGetLastError();
-    }
     return prec == ENS_FP32 ? dispatch_n<float>(n, pass, variant, mem, count, stage, tw, s)
                             : dispatch_n<double>(n, pass, variant, mem, count, stage, tw, s);
 }
