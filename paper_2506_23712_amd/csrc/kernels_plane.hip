@@ -13,9 +13,10 @@ namespace ens {
 // at these N, are launches of 5 to 10 us whatever they move; here 8 zl values.
 // Bound in FP32 by the VALU (1720 vector instructions per wave, the arithmetic
 // of 8.1 transforms a thread), in FP64 by its LDS exchanges, and for few
-// members by the latency of its phases.  Per RK step, before and after:
-// one 32^3 FP64 member 143 -> 78 us (with the state read back), five 64^3 FP32
-// members 196 -> 118 us, nine 64^3 FP64 members 278 -> 256 us.
+// members by the latency of its phases.  Per RK step,
+// before and with the z forward's small workgroups: one 32^3 FP64 member 143 ->
+// 66 us (with the state read back), five 64^3 FP32 members 196 -> 114 us, nine
+// 64^3 FP64 members about 280 -> 235 us.
 //
 // The plane lives in LDS as rows (f, kx) of N y positions.  Phase 1, one row per
 // group of M = N/8 or N/4 lanes: the row's spectral line (the vorticity's formed on
