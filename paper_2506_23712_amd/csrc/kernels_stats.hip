@@ -476,25 +476,35 @@ __global__ void __launch_bounds__(256, 2) k_gxstats(const MemberDev *__restrict_
     }
 }
 
-// One workgroup per member: moments += sum over blocks.  Thread (g, i) adds sum
-// i of every 32nd block, in order, and the 32 group sums are added in order
-// (deterministic); a row of partials is one 256-byte read.  One reduction tree
-// after another over the 26 sums took 34 us, this 6 us.
+// One workgroup per member: moments += sum over blocks, as a tree over 256
+// strided sums (deterministic; the tree's rounding is that of its last levels,
+// 0.6 u rms, where adding 32 sums one after another rounds to 1.4 u).  Thread
+// (g, i) forms the sums v = g, g + 32, ... of moment i and the tree's levels
+// among them, the groups the five levels left; a row of partials is one
+// 256-byte read.  One tree after another over the 26 sums took 34 us, all of
+// them at once 6 us.
 __global__ void __launch_bounds__(1024) k_stats_reduce(const MemberDev *__restrict__ mems, long long nblocks) {
     __shared__ double red[32][33];
     const MemberDev &md = mems[blockIdx.x];
     const int i = threadIdx.x & 31, g = threadIdx.x >> 5;
-    double x = 0.0;
-#pragma unroll 4
-    for (long long b = g; b < nblocks; b += 32) x += md.partials[b * 32 + i];
-    red[g][i] = x;
-    __syncthreads();
-    if (threadIdx.x < 26) {
-        double sum = 0.0;
+    double x[8];
 #pragma unroll
-        for (int k = 0; k < 32; k++) sum += red[k][threadIdx.x];
-        md.moments[threadIdx.x] += sum;
+    for (int k = 0; k < 8; k++) {
+        x[k] = 0.0;
+        for (long long b = g + 32 * k; b < nblocks; b += 256) x[k] += md.partials[b * 32 + i];
     }
+#pragma unroll
+    for (int k = 4; k > 0; k >>= 1)
+#pragma unroll
+        for (int j = 0; j < k; j++) x[j] += x[j + k];
+    red[g][i] = x[0];
+    __syncthreads();
+#pragma unroll
+    for (int s = 16; s > 0; s >>= 1) {
+        if (g < s) red[g][i] += red[g + s][i];
+        __syncthreads();
+    }
+    if (threadIdx.x < 26) md.moments[threadIdx.x] += red[0][threadIdx.x];
     // snapshot sums of the member's energy and dissipation (its last step's
     // values, those of the field this snapshot sees) and the snapshot count
     if (threadIdx.x == 0) {
@@ -504,18 +514,17 @@ __global__ void __launch_bounds__(1024) k_stats_reduce(const MemberDev *__restri
     }
 }
 
-// Workgroups per member of the persistent statistics pass: four row tiles
-// each (a workgroup clears, fills and flushes its histograms whatever its
-// share), but 512 in total, which are resident at once, up to 2048, and at
-// most one per row tile.  Always 2048: 133 us for nine 64^3 FP64 members, this 123.
+// Workgroups per member of the persistent statistics pass: about 2048 in
+// total over the launch, at most one per row tile.  (Fewer, with four tiles
+// each, take nine 64^3 FP64 members from 133 to 123 us, but a thread then adds
+// the values of four tiles one after another: 4 to 6 % more rounding in the
+// moments of 32^3 members.)
 static int xstats_grid(int n, int count) {
     const int tiles = n * n / (256 / (n / 4));
-    long long total = (long long)tiles * count / 4;
-    total = total < 512 ? 512 : (total > 2048 ? 2048 : total);
-    long long per = (total + count - 1) / count;
+    int per = (2048 + count - 1) / count;
     if (per > tiles) per = tiles;
     if (per > 512) per = 512;
-    return per < 1 ? 1 : (int)per;
+    return per < 1 ? 1 : per;
 }
 
 // ---------------------------------------------------------------- launchers
