@@ -149,7 +149,8 @@ ens_status ens_member_init(ens_ctx *ctx, const ens_member_desc *d, void *dev_wor
  * (modes outside D are ignored; m_x = 0 entries are used as given). */
 ens_status ens_member_set_state(ens_ctx *ctx, int32_t m, const double *dev_uhat, void *stream);
 
-/* Write member m's velocity into a device array in the canonical layout. */
+/* Write member m's velocity into a device array of doubles (8-byte aligned) in
+ * the canonical layout. */
 ens_status ens_member_get_state(ens_ctx *ctx, int32_t m, double *dev_uhat, void *stream);
 
 /* ------------------------------------------------------------ time stepping */

@@ -191,6 +191,10 @@ __global__ void __launch_bounds__(256) k_set_state(const MemberDev *__restrict__
     reinterpret_cast<L2<P> *>(md.q)[i] = z;
 }
 
+// A complex value of a caller's array of doubles, which need not be 16-byte
+// aligned (the store is one 16-byte instruction either way).
+typedef double UnalignedCx __attribute__((ext_vector_type(2), aligned(8)));
+
 // Bound by the FP64 array it writes.  A workgroup takes 1024 consecutive entries
 // of one (component, z) plane, so that only the row of an entry is divided out
 // (by a 32-bit multiplication: i / nh = i * magic >> 32 for i < n nh <= 2^20,
@@ -209,18 +213,18 @@ __global__ void __launch_bounds__(256) k_get_state(const MemberDev *__restrict__
     const bool zin = mz >= -K && mz <= K;
     const int iz = mz >= 0 ? mz : mz + 2 * K + 1;
     const L2<P> *src = reinterpret_cast<const L2<P> *>(md.uh) + ((long long)comp * (2 * K + 1) + (zin ? iz : 0)) * zp;
-    double2 *out = reinterpret_cast<double2 *>(dst) + ((long long)comp * n + zi) * plane;
+    UnalignedCx *out = reinterpret_cast<UnalignedCx *>(dst) + ((long long)comp * n + zi) * plane;
     const uint32_t i0 = blockIdx.x * 1024 + threadIdx.x;
-    double2 v[4];
+    UnalignedCx v[4];
 #pragma unroll
     for (int u = 0; u < 4; u++) {
         const uint32_t i = i0 + 256 * u;
         const int yi = (int)__umulhi(i, magic), kx = (int)(i - (uint32_t)yi * nh);
         const int my = yi <= n / 2 ? yi : yi - n;
-        v[u] = double2{0.0, 0.0};
+        v[u] = UnalignedCx{0.0, 0.0};
         if (zin && i < plane && kx <= K && my >= -K && my <= K) {
             const L2<P> x = src[(my >= 0 ? my : my + 2 * K + 1) * (K + 1) + kx];
-            v[u] = double2{(double)x.x, (double)x.y};
+            v[u] = UnalignedCx{(double)x.x, (double)x.y};
         }
     }
 #pragma unroll
