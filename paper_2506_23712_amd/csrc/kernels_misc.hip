@@ -195,13 +195,14 @@ __global__ void __launch_bounds__(256) k_set_state(const MemberDev *__restrict__
 // aligned (the store is one 16-byte instruction either way).
 typedef double UnalignedCx __attribute__((ext_vector_type(2), aligned(8)));
 
-// Bound by the FP64 array it writes.  A workgroup takes 1024 consecutive entries
+// Bound by the FP64 array it writes.  A workgroup takes 256 consecutive entries
 // of one (component, z) plane, so that only the row of an entry is divided out
 // (by a 32-bit multiplication: i / nh = i * magic >> 32 for i < n nh <= 2^20,
 // magic = ceil(2^32 / nh)) and a plane or row without retained modes is
-// written without a look at the state.  With one entry per thread and its
-// place divided out in 64 bits the 256^3 FP64 state took 116 us, so 104 us (5.1 TB/s
-// of reads and writes).
+// written without a look at the state.  One entry per thread: the waves that wait
+// are enough, and four entries 256 apart per thread were slower from n = 256
+// (us, 256^3 and 512^3 FP64: place divided out in 64 bits 108 and 805, four
+// entries 99 and 874, this 88 and 691, 6.0 TB/s of reads and writes).
 template <typename P>
 __global__ void __launch_bounds__(256) k_get_state(const MemberDev *__restrict__ mp, double *__restrict__ dst, uint32_t magic) {
     const MemberDev &md = *mp;
@@ -210,26 +211,17 @@ __global__ void __launch_bounds__(256) k_get_state(const MemberDev *__restrict__
     const long long zp = md.zp;
     const int comp = (int)blockIdx.z, zi = (int)blockIdx.y;
     const int mz = zi <= n / 2 ? zi : zi - n;
-    const bool zin = mz >= -K && mz <= K;
-    const int iz = mz >= 0 ? mz : mz + 2 * K + 1;
-    const L2<P> *src = reinterpret_cast<const L2<P> *>(md.uh) + ((long long)comp * (2 * K + 1) + (zin ? iz : 0)) * zp;
-    UnalignedCx *out = reinterpret_cast<UnalignedCx *>(dst) + ((long long)comp * n + zi) * plane;
-    const uint32_t i0 = blockIdx.x * 1024 + threadIdx.x;
-    UnalignedCx v[4];
-#pragma unroll
-    for (int u = 0; u < 4; u++) {
-        const uint32_t i = i0 + 256 * u;
-        const int yi = (int)__umulhi(i, magic), kx = (int)(i - (uint32_t)yi * nh);
-        const int my = yi <= n / 2 ? yi : yi - n;
-        v[u] = UnalignedCx{0.0, 0.0};
-        if (zin && i < plane && kx <= K && my >= -K && my <= K) {
-            const L2<P> x = src[(my >= 0 ? my : my + 2 * K + 1) * (K + 1) + kx];
-            v[u] = UnalignedCx{(double)x.x, (double)x.y};
-        }
+    const uint32_t i = blockIdx.x * 256 + threadIdx.x;
+    if (i >= plane) return;
+    const int yi = (int)__umulhi(i, magic), kx = (int)(i - (uint32_t)yi * nh);
+    const int my = yi <= n / 2 ? yi : yi - n;
+    UnalignedCx v = {0.0, 0.0};
+    if (kx <= K && my >= -K && my <= K && mz >= -K && mz <= K) {
+        const int iy = my >= 0 ? my : my + 2 * K + 1, iz = mz >= 0 ? mz : mz + 2 * K + 1;
+        const L2<P> x = reinterpret_cast<const L2<P> *>(md.uh)[((long long)comp * (2 * K + 1) + iz) * zp + iy * (K + 1) + kx];
+        v = UnalignedCx{(double)x.x, (double)x.y};
     }
-#pragma unroll
-    for (int u = 0; u < 4; u++)
-        if (i0 + 256 * u < plane) out[i0 + 256 * u] = v[u];
+    reinterpret_cast<UnalignedCx *>(dst)[((long long)comp * n + zi) * plane + i] = v;
 }
 
 hipError_t launch_set_state(int n, int prec, const MemberDev *mem, const double *src, hipStream_t s) {
@@ -243,7 +235,7 @@ hipError_t launch_set_state(int n, int prec, const MemberDev *mem, const double 
 hipError_t launch_get_state(int n, int prec, const MemberDev *mem, double *dst, hipStream_t s) {
     const uint32_t nh = n / 2 + 1, plane = n * nh;
     const uint32_t magic = (uint32_t)(((1ull << 32) + nh - 1) / nh);
-    const dim3 grid((plane + 1023) / 1024, n, 3);
+    const dim3 grid((plane + 255) / 256, n, 3);
     if (prec == ENS_FP32) k_get_state<float><<<grid, 256, 0, s>>>(mem, dst, magic);
     else k_get_state<double><<<grid, 256, 0, s>>>(mem, dst, magic);
     return hipGetLastError();
