@@ -783,12 +783,15 @@ __global__ void __launch_bounds__(64, (XWCfg<P, N, EV>::MINW)) k_xpass_wave2(con
         }
         wave_fence();
         store_tile(cur, false);
+        // here, where the fewest registers are in use (with the next tile's values
+        // already gathered the FP32 n = 1024 pass spilled 72 bytes per lane); the
+        // atomic is one operation more that the wait below finds after its copies
+        if (stage == 0 && (!more || nxt.mem != cur.mem)) flush_max(cur.mem);
         if (more) {                                            // pair 0 of the next tile, in slot 1 - u
             wait_vm<D2 + S>();
             wave_fence();
             gather(v, slot(1 - u), slot(1 - u) + RW);
         }
-        if (stage == 0 && (!more || nxt.mem != cur.mem)) flush_max(cur.mem);
         if (!more) break;
         f -= nw;
         cur = nxt;
