@@ -1063,7 +1063,7 @@ ENS_API ens_status ens_autotune(ens_ctx *ctx, const int32_t *members, int32_t co
                 return go(P_YFWD, variant_of(ctx, P_YFWD, g.n, g.prec), 1);
             };
             for (int v = 0; v < pass_variants(pass); v++) {
-                if (!variant_distinct(pass, g.n, v)) continue;
+                if (!variant_distinct(pass, g.n, g.prec, v)) continue;
                 for (int w = 0; w < 2; w++) HIPCK(ctx, launch(v));
                 float v_ms = 1e30f;
                 for (int trial = 0; trial < 3; trial++) {

@@ -135,7 +135,7 @@ enum Pass { P_BAND = 0, P_ZINV = 1, P_YINV = 2, P_XPASS = 3, P_YFWD = 4, P_ZFWD 
 hipError_t launch_pass(int pass, int variant, int n, int prec, const MemberDev *mem, int count, int stage,
                        const void *tw, hipStream_t s);
 int pass_variants(int pass);
-bool variant_distinct(int pass, int n, int variant);   // false: the kernel of another variant (not timed)
+bool variant_distinct(int pass, int n, int prec, int variant);   // false: the kernel of another variant (not timed)
 // Whether x-pass variant `variant` at grid size n is the plane pass, which also
 // performs the y inverse and the y forward.  The plane pass and the y inverse
 // perform the band step at stage < 4 and leave it out at stage + 4.

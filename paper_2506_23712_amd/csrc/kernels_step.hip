@@ -579,18 +579,9 @@ __global__ void __launch_bounds__((XCfg<P, N, EV>::NTH), (XCfg<P, N, EV>::MINB))
 // at strides that share banks, and the table kept an eighth wave off the
 // compute unit (LDS active 70 % of the pass; 219 -> 208 us for one 256^3
 // member without it).
-// Whether the pass has a valid tile for (N, E, complex size): a line within
-// one wave, whole 16-byte vectors per output tile, at least one wave-sized
-// copy per field and a vector-memory count that fits its counter.
-constexpr bool xwave_ok(int N, int E, int CS) {
-    const int M = N / (E > N ? N : E), K = N / 3, CPV = 16 / CS;
-    if (M > 64 || 64 % M != 0) return false;
-    const int R = 64 / M, RWO = R * (K + 1), RV = RWO / CPV;
-    if (RWO % CPV != 0 || RV < 64) return false;
-    const int D2 = 2 * ((RV + 63) / 64), S = 3 * ((RWO / CPV + 63) / 64);
-    return D2 + S < 64;
-}
-
+// A tile is valid with a line within one wave, whole 16-byte vectors per output
+// tile, at least one wave-sized copy per field and a vector-memory count that
+// fits its counter.
 template <typename P, int N, int E_> struct XWCfg {
     static constexpr int K = N / 3, E = E_ > N ? N : E_, M = N / E;
     static constexpr int R = 64 / M;                           // rows per tile (one wave)
@@ -1155,31 +1146,22 @@ static hipError_t run_pass(int pass, int variant, const MemberDev *mem, int coun
     const Cx<P> *twp = reinterpret_cast<const Cx<P> *>(tw);
     switch (pass) {
     case P_ZINV: case P_YINV: case P_XPASS: case P_YFWD:
-        if (pass == P_XPASS && variant == 2) {
-            if constexpr (N >= 64) return run_xpass_dma<P, N, 8>(mem, count, stage, twp, s);
-            else return run_pencil<P, N, 8>(pass, mem, count, stage, twp, s);   // lines too short to stream
+        if (pass == P_XPASS) {
+            switch (xpass_kernel(N, sizeof(P) == 4, variant)) {
+            case 0: return run_pencil<P, N, 8>(pass, mem, count, stage, twp, s);
+            case 1: return run_pencil<P, N, 16>(pass, mem, count, stage, twp, s);
+            case 2: if constexpr (N >= 64) return run_xpass_dma<P, N, 8>(mem, count, stage, twp, s); break;
+            case 3: if constexpr (xpass_kernel(N, sizeof(P) == 4, 3) == 3) return run_xpass_dma<P, N, 16>(mem, count, stage, twp, s); break;
+            case 5:                                            // stage + 4: without the band step
+                if constexpr (plane_ok(N))
+                    return launch_plane(N, sizeof(P) == 4 ? ENS_FP32 : ENS_FP64, mem, count, stage & 3, stage < 4, tw, s);
+                break;
+            case 6: if constexpr (N >= 64) return run_xpass_wave2<P, N, (sizeof(P) == 4 ? 16 : 8)>(mem, count, stage, twp, s); break;
+            }
+            return hipErrorInvalidValue;
         }
-        if (pass == P_XPASS && variant == 5) {
-            // the plane pass where it exists; stage + 4: without the band step
-            if constexpr (plane_ok(N))
-                return launch_plane(N, sizeof(P) == 4 ? ENS_FP32 : ENS_FP64, mem, count, stage & 3, stage < 4, tw, s);
-        }
-        if (pass == P_XPASS && variant >= 4) {
-            // wave-private, pairs staged through two buffers: 16 (FP32) / 8 (FP64) values per thread
-            constexpr int EA = sizeof(P) == 4 ? 16 : 8, CS = (int)sizeof(Cx<P>);
-            if constexpr (N >= 64 && xwave_ok(N, EA, CS)) return run_xpass_wave2<P, N, EA>(mem, count, stage, twp, s);
-            else if constexpr (N >= 64) return run_xpass_dma<P, N, 8>(mem, count, stage, twp, s);
-            else return run_pencil<P, N, 8>(pass, mem, count, stage, twp, s);
-        }
-        if (pass == P_XPASS && variant == 3) {
-            // streamed, 16 values per thread (one LDS exchange per 256-point
-            // transform); FP32 only: FP64 would need more than 256 registers
-            if constexpr (N >= 128 && N <= 512 && sizeof(P) == 4) return run_xpass_dma<P, N, 16>(mem, count, stage, twp, s);
-            else if constexpr (N >= 64) return run_xpass_dma<P, N, 8>(mem, count, stage, twp, s);
-            else return run_pencil<P, N, 8>(pass, mem, count, stage, twp, s);
-        }
-        if (pass != P_XPASS && variant == 2) return run_pencil<P, N, 8, 2>(pass, mem, count, stage, twp, s);
-        if (pass != P_XPASS && variant == 3) return run_pencil<P, N, 16, 2>(pass, mem, count, stage, twp, s);
+        if (variant == 2) return run_pencil<P, N, 8, 2>(pass, mem, count, stage, twp, s);
+        if (variant == 3) return run_pencil<P, N, 16, 2>(pass, mem, count, stage, twp, s);
         return variant == 1 ? run_pencil<P, N, 16>(pass, mem, count, stage, twp, s)
                             : run_pencil<P, N, 8>(pass, mem, count, stage, twp, s);
     case P_ZFWD: {
@@ -1225,10 +1207,8 @@ hipError_t launch_pass(int pass, int variant, int n, int prec, const MemberDev *
                             : dispatch_n<double>(n, pass, variant, mem, count, stage, tw, s);
 }
 
-// Variants of the x pass that are another one's kernel: 4, and 5 where there
-// is no plane pass, are 6.
-bool variant_distinct(int pass, int n, int variant) {
-    return pass != P_XPASS || (variant != 4 && (variant != 5 || plane_ok(n)));
+bool variant_distinct(int pass, int n, int prec, int variant) {
+    return pass != P_XPASS || xpass_kernel(n, prec == ENS_FP32, variant) == variant;
 }
 
 int pass_variants(int pass) {

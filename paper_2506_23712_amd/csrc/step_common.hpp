@@ -30,6 +30,19 @@ __device__ __forceinline__ double block_sum(double v, double *red) {
 // precisions (135 KB for N = 64 in FP64): the plane pass exists for these N.
 constexpr bool plane_ok(int N) { return N <= 64; }
 
+// The x-pass variant whose kernel `variant` runs at grid size n: itself, or the
+// one that stands for it where it has no kernel of its own.  Lines of n < 64 are
+// too short to stream.  Streamed with 16 values per thread (one LDS
+// exchange per 256-point transform) in FP32 only: FP64 would need more than 256
+// registers.
+constexpr int xpass_kernel(int n, bool fp32, int variant) {
+    if (variant == 5 && plane_ok(n)) return 5;
+    if (variant >= 4) return n >= 64 ? 6 : 0;                   // wave-private, pairs staged through two buffers
+    if (variant == 3) return fp32 && n >= 128 && n <= 512 ? 3 : xpass_kernel(n, fp32, 2);
+    if (variant == 2) return n >= 64 ? 2 : 0;
+    return variant;
+}
+
 // ------------------------------------------------------------ pass configs
 // E = complex values per thread (a line of N uses N/E threads).  Variants of
 // E are compiled for the pencil passes and the x pass; the host picks one per
