@@ -1032,7 +1032,7 @@ ENS_API ens_status ens_autotune(ens_ctx *ctx, const int32_t *members, int32_t co
     // scratch buffers, so the members' state is unchanged by tuning.
     for (const Group &g : pl->groups) {
         const int cnt = (int)g.ids.size();
-        for (int pass : {P_ZINV, P_YINV, P_XPASS, P_YFWD}) {
+        for (int pass : {P_ZINV, P_YINV, P_YFWD, P_XPASS}) {       // the x pass last: it is timed beside the tuned y passes
             const std::string key = variant_key(pass, g.n, g.prec);
             auto hit = cache.find(key);
             if (hit != cache.end() && hit->second >= 0 && hit->second < pass_variants(pass)) {
@@ -1048,8 +1048,8 @@ ENS_API ens_status ens_autotune(ens_ctx *ctx, const int32_t *members, int32_t co
             // the y inverse (already tuned) that writes its inputs: variants
             // within a few per cent of each other in isolation rank differently
             // there.  Where one variant is the plane pass, which needs no y passes,
-            // the others are timed with a y forward too (the band step, which it
-            // also takes over, writes the state and is left out on both sides).
+            // the others are timed with the tuned y forward too (the band step, which
+            // it also takes over, writes the state and is left out on both sides).
             const bool xp = pass == P_XPASS;
             bool plane = false;
             for (int v = 0; v < pass_variants(pass); v++) plane = plane || (xp && plane_pass(g.n, v));

@@ -1,4 +1,4 @@
-"""What the autotuner times: every kernel once."""
+"""What the autotuner times: every kernel once, the x pass beside tuned y passes."""
 import pytest
 
 pytestmark = pytest.mark.gpu
@@ -30,3 +30,14 @@ def test_every_x_pass_kernel_is_timed_once(n, prec):
     assert {k: x.count(k) for k in x} == {k: RUNS for k in x}
     # 8 and 16 values per thread, streamed (two of them in FP32 from n = 128), wave-private, plane pass
     assert len(set(x)) == 2 + (n >= 64) + (n >= 128 and prec == "fp32") + (n >= 64) + (n <= 64)
+
+
+@pytest.mark.parametrize("n,prec", [(32, "fp64"), (64, "fp32"), (128, "fp64")])
+def test_the_y_passes_are_tuned_before_the_x_pass(n, prec):
+    """The plane pass stands for the y inverse, an x pass and the y forward; the
+    separate passes it is compared with are the tuned ones."""
+    names = tuned(n, prec)
+    first = next(i for i, k in enumerate(names) if k.startswith(("k_xpass", "k_plane")))
+    for p in ("k_yinv", "k_yfwd"):
+        kinds = {k for k in names if k.startswith(p + "<")}
+        assert len(kinds) == 4 and kinds == {k for k in names[:first] if k.startswith(p + "<")}
