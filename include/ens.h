@@ -215,8 +215,11 @@ ens_status ens_get_diag(ens_ctx *ctx, int32_t m, ens_diag *out);
  * each launch after the y inverse that writes its inputs, and for n <= 64
  * with the y forward after it, against the plane pass alone).  Only scratch buffers are written:
  * member state is unchanged.  `cache_path` (may be NULL) names a text file of
- * "pass:n:precision variant" lines: entries found there are used without
- * timing, and the file is rewritten with the full table.  Synchronises. */
+ * "pass:n:precision variant" lines after a first line that names the library's
+ * set of kernels: entries found there are used without timing, and the file is
+ * rewritten with the full table.  A file whose first line names another set, or
+ * none (as written before there were several), has variant numbers that meant
+ * other kernels: it is timed anew and replaced.  Synchronises. */
 ens_status ens_autotune(ens_ctx *ctx, const int32_t *members, int32_t count, void *stream,
                         const char *cache_path);
 

@@ -979,10 +979,18 @@ std::string variant_key(int pass, int n, int prec) {
     return std::string(pass_name(pass)) + ":" + std::to_string(n) + ":" + (prec == ENS_FP32 ? "fp32" : "fp64");
 }
 
-// cache file: one "key variant" pair per line, '#' comments
+// First line of a cache file: the set of kernels its choices were made among.
+// The number goes up whenever a variant number's kernel changes or a variant is
+// added (2: the plane pass as x-pass variant 5, 4 the kernel of 6, other
+// workgroups of the y and z passes for n <= 64; files without the line: 1).
+const char *const kCacheHead = "# libensdns kernel set 2";
+
+// cache file: kCacheHead, then one "key variant" pair per line, '#' comments.
+// A file of another kernel set has no entries.
 void read_cache(const char *path, std::map<std::string, int> &out) {
     std::ifstream f(path);
     std::string line;
+    if (!std::getline(f, line) || line != kCacheHead) return;
     while (std::getline(f, line)) {
         if (line.empty() || line[0] == '#') continue;
         std::istringstream is(line);
@@ -1087,7 +1095,7 @@ ENS_API ens_status ens_autotune(ens_ctx *ctx, const int32_t *members, int32_t co
     drop_graphs(ctx);
     if (cache_path) {
         std::ofstream f(cache_path);
-        f << "# libensdns kernel variants (pass:n:precision variant); 0 = 8, 1 = 16 values per thread, 2 and 3 = the same with twice the lines per workgroup (y/z passes) or the streamed x pass with 8 and 16, 4 and 6 = wave-private streamed x pass, 5 = plane pass (n <= 64, else as 6)\n";
+        f << kCacheHead << "\n# kernel variants (pass:n:precision variant); 0 = 8, 1 = 16 values per thread, 2 and 3 = the same with twice the lines per workgroup (y/z passes) or the streamed x pass with 8 and 16, 4 and 6 = wave-private streamed x pass, 5 = plane pass (n <= 64, else as 6)\n";
         for (auto &kv : cache) f << kv.first << " " << kv.second << "\n";
     }
     return ENS_OK;
