@@ -183,12 +183,9 @@ def roofline(res):
     over its average launch duration."""
     from paper_2506_23712_amd import profiling
     (n, prec), k, count, avg_ms, launches, fused = dominant_kernel(res)
-    if k == "zfwd_update":
-        bytes_launch = sum(profiling.zfwd_stage_bytes(n, prec, 1, fused)) * count
-    else:
-        bytes_launch = pass_bytes(n, prec)[k] * count
-    gbs = bytes_launch / (avg_ms * 1e-3) / 1e9
     v = res["variants"].get(f"{k}:{n}:{prec}")
+    bytes_launch = profiling.launch_bytes(k, n, prec, v) * count
+    gbs = bytes_launch / (avg_ms * 1e-3) / 1e9
     pname = profiling.kernel_name(k, n, prec, v)
     return {"bound": "hbm", "achieved": round(gbs, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
             "frac": round(gbs / HBM_PEAK_GBS, 4), "traffic": measured_traffic(res["name"], pname),

@@ -62,6 +62,26 @@ def pass_bytes(n: int, prec: str) -> dict:
     }
 
 
+def plane_bytes(n: int, prec: str) -> tuple:
+    """(read, write) algorithmic bytes of the plane pass (x-pass variant 5 of
+    n <= 64) for one member: the 5 z-inverse fields read, the 3 fields of the y
+    forward written; nothing of the y passes between goes through memory."""
+    K = n // 3
+    cs = 16 if prec == "fp64" else 8
+    zl = n * (2 * K + 1) * (K + 1)
+    return 5 * zl * cs, 3 * zl * cs
+
+
+def launch_bytes(pass_name: str, n: int, prec: str, variant=None) -> float:
+    """Algorithmic bytes of one launch of a pass's kernel for one member (the
+    z forward: the kernel of the middle RK stage)."""
+    if pass_name == "zfwd_update":
+        return sum(zfwd_stage_bytes(n, prec, 1, variant == 1))
+    if pass_name == "xpass" and variant == 5 and n <= 64:
+        return sum(plane_bytes(n, prec))
+    return pass_bytes(n, prec)[pass_name]
+
+
 def zfwd_stage_bytes(n: int, prec: str, stage: int, fused: bool = False) -> tuple:
     """(read, write) algorithmic bytes of the z forward + update of one RK
     stage for one member: the 3 z-line fields and u_hat read, u_hat written;
@@ -188,8 +208,8 @@ def write_summary(n: int, counts, out: str, trace: str | None = None, workloads=
         for k in ("zinv", "yinv", "xpass", "yfwd", "zfwd_update"):
             for name, v in sorted(t["kernels"].items()):
                 short = name.replace("ens::", "")
-                if not (short.startswith(f"k_{k}<") or (k == "xpass" and short.startswith(("k_xpass_dma<", "k_xpass_wave<",
-                                                                                          "k_xpass_wave2<")))):
+                if not (short.startswith(f"k_{k}<") or (k == "xpass" and short.startswith(("k_xpass_dma<", "k_xpass_wave2<",
+                                                                                          "k_plane<")))):
                     continue
                 if f", {n}" not in short or ("float" in short) != (prec == "fp32"):
                     continue
@@ -198,6 +218,8 @@ def write_summary(n: int, counts, out: str, trace: str | None = None, workloads=
                 if st:                                     # one RK stage: its own register traffic
                     r1, w1 = zfwd_stage_bytes(n, prec, int(st.group(1)), st.group(2) == "true")
                     ar, aw = r1 * cnt, w1 * cnt
+                if short.startswith("k_plane<"):
+                    ar, aw = (b * cnt for b in plane_bytes(n, prec))
                 us = avg.get(name)
                 rows.append((wl, short, ar / 1e9, aw / 1e9, v["fetch_bytes"] / 1e9, v["write_bytes"] / 1e9,
                              (v["fetch_bytes"] + v["write_bytes"]) / (ar + aw), t["source_hash"], us,
