@@ -230,7 +230,10 @@ ens_status ens_autotune(ens_ctx *ctx, const int32_t *members, int32_t count, voi
  * z forward of the first two stages also performs the next stage's z inverse
  * from the velocity it has just updated, so each step reads the velocity back
  * once instead of three times, and inside one ens_step call of several steps
- * the last stage does the same for the next step (default for n <= 512). */
+ * the last stage does the same for the next step (default for n <= 512).
+ * Where the x pass is the plane pass (pass 3 variant 5 at n <= 64, the default
+ * there) it stands for the y passes too: their variants are accepted and kept,
+ * and take effect with any other x-pass variant. */
 ens_status ens_set_variant(ens_ctx *ctx, int32_t pass, int32_t n, int32_t precision, int32_t variant);
 ens_status ens_get_variant(const ens_ctx *ctx, int32_t pass, int32_t n, int32_t precision, int32_t *variant);
 

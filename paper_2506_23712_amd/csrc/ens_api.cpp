@@ -291,11 +291,10 @@ bool zinv_fused(const ens_ctx *ctx, int pass, int stage, int n, int prec, StepKi
     return pass == P_ZINV && variant_of(ctx, P_ZFWD, n, prec) == 1 && (stage > 0 || k.zinv0_done);
 }
 
-// Passes another launch of the stage performs: the band step (the y inverse or
-// the plane pass does it), the fused z inverse, and with the plane pass (an
-// x-pass variant) the y passes.
+// Passes another launch of the stage performs: the fused z inverse, and with
+// the plane pass (an x-pass variant) the y passes.  (The band step, P_BAND, has
+// no launch of its own: the y inverse or the plane pass performs it.)
 bool pass_done(const ens_ctx *ctx, int pass, int stage, int n, int prec, StepKind k) {
-    if (pass == P_BAND) return true;
     if ((pass == P_YINV || pass == P_YFWD) && plane_pass(n, variant_of(ctx, P_XPASS, n, prec))) return true;
     return zinv_fused(ctx, pass, stage, n, prec, k);
 }
@@ -311,7 +310,7 @@ hipError_t enqueue_group(const ens_ctx *ctx, const Group &g, hipStream_t s, Step
     const int cnt = (int)g.ids.size();
     hipError_t e;
     for (int stage = 0; stage < 3; stage++)
-        for (int pass = P_BAND; pass <= P_ZFWD; pass++) {
+        for (int pass = P_ZINV; pass <= P_ZFWD; pass++) {
             if (pass_done(ctx, pass, stage, g.n, g.prec, k)) continue;
             if ((e = launch_pass(pass, launch_variant(ctx, pass, stage, g.n, g.prec, k), g.n, g.prec, g.dev, cnt,
                                  stage, g.tw, s)))
@@ -359,7 +358,7 @@ hipError_t enqueue_step(const ens_ctx *ctx, const Plan &pl, hipStream_t s, Prof 
     for (int stage = 0; stage < 3; stage++) {
         for (const Group &g : pl.groups) {
             const int cnt = (int)g.ids.size();
-            for (int pass = P_BAND; pass <= P_ZFWD; pass++) {
+            for (int pass = P_ZINV; pass <= P_ZFWD; pass++) {
                 if (pass_done(ctx, pass, stage, g.n, g.prec, k)) continue;
                 const int v = launch_variant(ctx, pass, stage, g.n, g.prec, k);
                 if ((e = rec(pass, [&] { return launch_pass(pass, v, g.n, g.prec, g.dev, cnt, stage, g.tw, s); }))) return e;
