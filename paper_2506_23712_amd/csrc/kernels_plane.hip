@@ -11,12 +11,16 @@ namespace ens {
 // stage has one launch for three passes and the band step.  The three passes
 // move 5 zl + 6 yl, 9 yl and 3 yl + 3 zl values per member (zl = 2/3 yl) and,
 // at these N, are launches of 5 to 10 us whatever they move; here 8 zl values.
-// Bound in FP32 by the VALU (1720 vector instructions per wave, the arithmetic
-// of 8.1 transforms a thread), in FP64 by its LDS exchanges, and for few
-// members by the latency of its phases.  Per RK step,
-// before and with the z forward's small workgroups: one 32^3 FP64 member 143 ->
-// 66 us (with the state read back), five 64^3 FP32 members 196 -> 114 us, nine
-// 64^3 FP64 members about 280 -> 235 us.
+// FP32: 1725 vector instructions per wave (the arithmetic of 8.1 transforms a
+// thread) keep the VALU active in 50 % of the launch's cycles and the LDS in 25 %
+// (12 members of 64^3).  FP64: VALU 28 %, LDS 30 % (28 % of that bank conflicts),
+// the waves waiting in half of their cycles: one workgroup of 8 waves on a compute
+// unit, whose phases are apart by barriers, and 585 workgroups (nine 64^3
+// members) are 2.3 rounds of 256.  For few members the latency of the phases is
+// the time.  Per RK step, before and now: one 32^3 FP64 member with its state read
+// back 143 -> 66 us, five 64^3 FP32 members 196 -> 114 us, nine 64^3 FP64 members
+// (profiled launches, y inverse, x pass, y forward and band step) 228 -> 161 us, 47
+// of 64^3 FP32 528 -> 321 us.
 //
 // The plane lives in LDS as rows (f, kx) of N y positions.  Phase 1, one row per
 // group of M = N/8 or N/4 lanes: the row's spectral line (the vorticity's formed on
@@ -45,8 +49,9 @@ template <typename P, int N> struct PlaneCfg {
     static constexpr int MINW = N == 64 ? (sizeof(P) == 4 ? 4 : 2) : 1;   // waves per SIMD
     static constexpr int RPW = 64 / M;                         // columns of a wave in phase 2
     // FP64: each thread's twiddles in registers (a table in LDS is read at
-    // strides that share banks, and the LDS is what bounds FP64); FP32: in LDS
-    // (its registers are what bound the workgroups per compute unit)
+    // strides that share banks, and its registers are free: the LDS admits one
+    // workgroup per compute unit); FP32: in LDS (registers are what bound its
+    // workgroups per compute unit)
     static constexpr bool REGTW = sizeof(P) == 8;
     static constexpr int NB = NT >= 256 ? 256 : 128;           // threads of the band step
     __device__ static __forceinline__ int sw(int p) { return p ^ ((p >> 3) & 7); }

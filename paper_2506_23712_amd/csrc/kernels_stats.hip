@@ -318,9 +318,12 @@ __global__ void __launch_bounds__(256, 2) k_gxstats(const MemberDev *__restrict_
         }
     };
     // Each pair is loaded one pair ahead; across tiles in FP32 only: in FP64 the
-    // second pair of registers fits beside the transforms, not beside the
-    // pointwise work.  (FP64 without it: 577 us for seven members of 128^3,
-    // with it 526 us.)
+    // second pair of registers fits beside the transforms (n = 128: no spill; 64 and
+    // 256 spill 17 and 30 registers and gain all the same), not beside the
+    // pointwise work.  FP64 without it and with it: 577 -> 526 us for seven
+    // members of 128^3; a whole snapshot, one 256^3 member 967 -> 862 us, three
+    // 2806 -> 2526, one 512^3 8697 -> 8119, nine 64^3 206 -> 161 (with the one-pass
+    // reduction of the moments, 28 us of each).
     constexpr bool PFX = sizeof(P) == 4;
     Cx<P> ra[E], rb[E];
     if (PFX && (int)blockIdx.x < ntiles) load_pair(blockIdx.x, 0, ra, rb);

@@ -1222,12 +1222,18 @@ int default_variant(int pass, int n, int prec) {
     // x pass: the plane pass where it exists; the wave-private pass from n = 256
     // (one member, us a step: 256 FP32 307 against 311 and more, 256 FP64 582 /
     // 676, 512 FP32 2248 / 2879) and at 128 in FP64 (four members 295 / 340); at
-    // 128 in FP32 the streamed pass with 16 values per thread (six members 222 /
-    // 232); at 1024 the streamed one with 8 (the wave-private one spills)
+    // 128 in FP32 the streamed pass with 16 values per thread (six members 211 /
+    // 220); at 1024 the streamed one with 8, to which a caller that tunes prefers
+    // the wave-private one (34.0 / 20.7 ms)
     if (pass == P_XPASS)
         return plane_ok(n) ? 5 : n == 1024 ? 2 : (n == 128 && prec == ENS_FP32) ? 3 : 6;
     // y and z passes: 8 values per thread; 16 in FP32 only for the y inverse at
-    // n = 256 (287 against 303 us a step) and, not measured again, at n = 1024
+    // n = 256 and for all three at n = 1024.  us a step in FP32, 8 / 16 values, z
+    // inverse (one launch), y inverse, y forward: 64^3 x 12 11.2 / 13.8, 51 / 59,
+    // 34 / 40; 128^3 x 4 21.5 / 23.1, 114 / 121, 64 / 62; 256^3 41.6 / 41.0,
+    // 294 / 279, 140 / 136; 512^3 352 / 368, 2412 / 2502, 1113 / 1147; 1024^3
+    // 4249 / 3816, 25362 / 22076, 11186 / 10126.  FP64: 32^3 x 4 8.7 / 11.7,
+    // 29 / 42, 21 / 27.
     if (pass == P_YINV) return prec == ENS_FP32 && n >= 256 && n != 512 ? 1 : 0;
     if (pass == P_ZINV || pass == P_YFWD) return prec == ENS_FP32 && n == 1024 ? 1 : 0;
     // fused z forward: 0.4-1.8 % faster per step up to n = 512 (both

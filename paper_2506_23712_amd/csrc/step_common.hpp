@@ -99,7 +99,8 @@ template <typename P, int N, int E_, int TM = 1> struct Cfg {
     // threads for a 64^3 member, 2 for a 32^3 one, on 256 compute units).
     // Values per thread: 8; 4 for N <= 64, where a wave's own instructions are
     // the time (us a step, one 32^3 FP64 member 37 -> 29, nine 64^3 FP64 members
-    // 88 -> 76, 47 of 64^3 FP32 equal), and in FP64 at N = 128 (eight members 468
+    // 88 -> 76, 47 of 64^3 FP32 equal; against 512 threads with 8 values: 56 / 29,
+    // 74 / 76, 199 / 190), and in FP64 at N = 128 (eight members 468
     // -> 454; FP32 191 -> 199; FP64 at N = 256 484 -> 567); 16 at N = 1024.
     static constexpr int EZ = N <= 64 || (sizeof(P) == 8 && N == 128) ? 4 : N <= 512 ? 8 : 16, MZ = N / EZ;
     static constexpr int TZ = N <= 64 ? (128 / MZ > TL ? 128 / MZ : TL) : N <= 512 ? TL : 512 / MZ;
