@@ -269,7 +269,7 @@ hipError_t launch_fill_f64(double *p, long long n, double v, hipStream_t s) {
 // lines: runs of 256 bytes at n = 256, 128 at 512, 64 at 1024 (where whole
 // 128-byte runs, 128 KiB, were slower).  With 256 threads whatever n, n = 512
 // FP32 moved runs of 64 bytes and n = 1024 of 32 bytes: 302 us for 87041 lines
-// of n = 512 FP32, now 155 (4.6 TB/s).  Neighbouring tiles run on one XCD
+// of n = 512 FP32, now 160 (4.4 TB/s).  Neighbouring tiles run on one XCD
 // (xcd_tile): where `lines` is no multiple of T a run straddles a line that its
 // neighbour reads or writes the rest of.  Twiddles from LDS, as in the time-step
 // passes.
